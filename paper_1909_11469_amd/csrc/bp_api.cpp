@@ -48,12 +48,6 @@ int hip_fail(hipError_t e, const char* what) {
         if (_e != hipSuccess) return hip_fail(_e, what);    \
     } while (0)
 
-int kpad(int K) {
-    int p = 2;
-    while (p < K) p <<= 1;
-    return p;
-}
-
 struct DeviceGuard {
     int prev = -1;
     explicit DeviceGuard(int dev) {
@@ -77,7 +71,9 @@ struct HostLayout {
     std::vector<int> tile_start;      // [T+1]
     std::vector<int> tile_slot;       // [T+1] node_ptr[tile_start]
     int tile_nodes_max = 1;           // most nodes in one regular tile
+    int tile_slots_max = 1;           // most slots in one regular tile
     int tile_big = 0;                 // 1 if some node's slots exceed the tile limit
+    int pairs_route = 0;              // [E][K] layout: 1 if the graph takes k_eval_pairs
     int no_mfma = 0;                  // BP_FLAG_NO_MATRIX_CORES
     int mfma_bf16 = 0;                // BP_FLAG_BF16_MATRIX_CORES
     int sparse_reserved = 0;          // BP_FLAG_SPARSE_BUFFERS on a log-odds graph
@@ -427,14 +423,32 @@ int build_layout(const bp_graph_desc* d, HostLayout& L) {
                                                     : std::max(1, kTileFloatsGeneric / (int)K);
     const int node_lim = L.layout == kLayoutLogOdds ? kTileNodesLogOdds
                                                     : std::min(kTileNodesMax, slot_lim);
+    // k_eval_pairs takes per-slot tables (a thread per slot would read them K * K
+    // floats apart) and every shared table over 16 states that no kernel of its own
+    // exists for: K other than 32 and 64, and these beside a node over the tile
+    // limit.  Up to 16 states a thread per slot is the faster one (ten RnBP sweeps
+    // of a 300 x 300 grid, K = 5: 487 us there).  Its tiles are filled less, for
+    // enough blocks.
+    int max_deg = 0;
+    for (long long i = 0; i < N; ++i) max_deg = std::max(max_deg, L.node_ptr[i + 1] - L.node_ptr[i]);
+    L.pairs_route = L.layout == kLayoutGeneric && K > 2 &&
+                    (L.pair == kPairDense ||
+                     (K > 16 && ((K != 32 && K != 64) || max_deg > slot_lim)));
+    int slot_fill = slot_lim, node_fill = node_lim;
+    if (L.pairs_route) {
+        const long long most = L.pair == kPairDense ? kPairsFloatsDense : kPairsFloatsShared;
+        const long long f = std::min(most, std::max<long long>(kPairsFloatsMin, E * K / kPairsTiles));
+        slot_fill = std::max(1, (int)(f / K));
+        node_fill = std::min(node_lim, slot_fill);
+    }
     L.tile_start.clear();
     long long n = 0;
     while (n < N) {
         L.tile_start.push_back((int)n);
         const long long s_begin = L.node_ptr[n];
         long long m = n;
-        while (m < N && (m - n) < node_lim && (L.node_ptr[m + 1] - s_begin) <= slot_lim) ++m;
-        if (m == n) m = n + 1;  // oversize node
+        while (m < N && (m - n) < node_fill && (L.node_ptr[m + 1] - s_begin) <= slot_fill) ++m;
+        if (m == n) m = n + 1;  // a node of its own tile
         n = m;
     }
     L.tile_start.push_back((int)N);
@@ -443,13 +457,18 @@ int build_layout(const bp_graph_desc* d, HostLayout& L) {
     L.tiles4.clear();
     L.big4.clear();
     L.tile_nodes_max = 1;
+    L.tile_slots_max = 1;
     L.tile_big = 0;
     for (size_t i = 0; i + 1 < L.tile_start.size(); ++i) {
         if (L.tile_slot[i + 1] - L.tile_slot[i] > slot_lim)
             L.tile_big = 1;
-        else
+        else {
             L.tile_nodes_max = std::max(L.tile_nodes_max, L.tile_start[i + 1] - L.tile_start[i]);
+            L.tile_slots_max = std::max(L.tile_slots_max, L.tile_slot[i + 1] - L.tile_slot[i]);
+        }
     }
+    // slots of a node over the limit are taken a tile's worth at a time
+    if (L.tile_big) L.tile_slots_max = std::max(L.tile_slots_max, slot_fill);
     for (size_t i = 0; i + 1 < L.tile_start.size(); ++i) {
         const int q[4] = {L.tile_start[i], L.tile_start[i + 1], L.tile_slot[i], L.tile_slot[i + 1]};
         std::vector<int>& dstv = (q[3] - q[2] > slot_lim) ? L.big4 : L.tiles4;
@@ -753,7 +772,12 @@ static EvalArgs run_args(const bp_graph* g, int schedule, double eps, double p, 
     a.num_messages = (unsigned long long)L.E;
     a.num_nodes = L.N;
     a.tile_nodes_max = L.tile_nodes_max;
+    a.tile_slots_max = L.tile_slots_max;
     a.tile_big = L.tile_big;
+    a.pairs_route = L.pairs_route;
+    a.k_magic = (1u << 20) / (unsigned int)L.K + 1u;
+    for (a.k_wlog = 0; (1 << a.k_wlog) < L.K; ++a.k_wlog) {
+    }
     a.no_mfma = L.no_mfma;
     a.mfma_bf16 = L.mfma_bf16;
     a.rbp_k = (unsigned long long)rbp_k;
@@ -999,7 +1023,6 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
     const long long tune_end = tune ? (long long)tcand.size() * kTuneLaunches : 0;
     if (ev0) HIP_OK(hipEventRecord(ev0, s), "event record");
 
-    const int kp = kpad(L.K);
     const long long t_start = g->t_next;
     const int pair0 = g->cur_pair;
     float* const start_buf = g->cur();
@@ -1072,7 +1095,7 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
         }
         if (prof_window && in_chunk == 0) HIP_OK(hipEventRecord(kev[0], s), "event record");
         if (timed) HIP_OK(hipEventRecord(kev[2 * in_chunk], s), "event record");
-        HIP_OK(launch_eval(L.layout, kp, emode, a, s), "evaluation kernel");
+        HIP_OK(launch_eval(L.layout, emode, a, s), "evaluation kernel");
         if (timed) HIP_OK(hipEventRecord(kev[2 * in_chunk + 1], s), "event record");
         if (tuning && it % kTuneLaunches == kTuneLaunches - 1)
             HIP_OK(hipEventRecord(tev[2 * (it / kTuneLaunches) + 1], s), "event record");
@@ -1284,7 +1307,7 @@ int bp_marginals_device(bp_graph* g, float* out_device) {
         HIP_OK(launch_marginals_ragged(a, out_device, g->stream), "marginals kernel");
         return BP_OK;
     }
-    HIP_OK(launch_marginals(L.layout, kpad(L.K), g->at<int>(g->off.node_ptr), g->at<int>(g->off.rev),
+    HIP_OK(launch_marginals(L.layout, g->at<int>(g->off.node_ptr), g->at<int>(g->off.rev),
                             g->at<float>(g->off.unary), g->cur(), out_device, L.N, L.K,
                             g->stream),
            "marginals kernel");

@@ -31,6 +31,13 @@ constexpr int kTileNodesLogOdds = kTileSlotsLogOdds / 2;  // nodes per log-odds 
 #define BP_TILE_FLOATS_GENERIC 4096
 #endif
 constexpr int kTileFloatsGeneric = BP_TILE_FLOATS_GENERIC;  // [E][K] layout: tile slots = this / K
+// Tiles of the graphs that take k_eval_pairs: filled to kPairsFloatsMin..Max floats, so that
+// a small graph still gives about kPairsTiles tiles.  A node may still bring up to
+// kTileFloatsGeneric floats of its own.
+constexpr int kPairsFloatsMin = 512;
+constexpr int kPairsFloatsDense = 1024;
+constexpr int kPairsFloatsShared = 2048;
+constexpr int kPairsTiles = 1024;
 constexpr int kTileNodesMax = 2048;      // nodes per tile (owner index fits in u16)
 constexpr int kMaxK = 64;
 constexpr int kMaxKRagged = 128;  // largest K_i of a graph with per-variable state counts
@@ -163,7 +170,11 @@ struct EvalArgs {
     unsigned long long num_messages;
     int num_nodes;
     int tile_nodes_max;         // [E][K] layout: most nodes in one regular tile
+    int tile_slots_max;         // [E][K] layout: most slots in one regular tile
     int tile_big;               // [E][K] layout: 1 if some node's slots exceed a tile
+    int pairs_route;            // [E][K] layout: 1 if the graph takes k_eval_pairs
+    unsigned int k_magic;       // i / K = (i * k_magic) >> 20 for i < 16384
+    int k_wlog;                 // log2 of K rounded up to a power of two
     int no_mfma;                // K = 32 shared table on the vector units (not the matrix cores)
     int mfma_bf16;              // K = 32 shared table: BF16 operands on the matrix cores
     int hist0;                  // frontier RBP, K = 2 kernel: also count the first radix
@@ -212,10 +223,10 @@ hipError_t launch_batch_status(const BatchGraph* graphs, int num_graphs, unsigne
                                hipStream_t s);
 hipError_t launch_init_state(DevState* st, CounterLine* ctr, hipStream_t s);
 hipError_t launch_fill(float* p, float v, long long n, hipStream_t s);
-hipError_t launch_eval(int layout, int kp, int mode, const EvalArgs& a, hipStream_t s);
+hipError_t launch_eval(int layout, int mode, const EvalArgs& a, hipStream_t s);
 hipError_t launch_close_run(const EvalArgs& a, hipStream_t s);
 int logodds_blocks_per_cu(int mode);
-hipError_t launch_marginals(int layout, int kp, const int* node_ptr, const int* rev,
+hipError_t launch_marginals(int layout, const int* node_ptr, const int* rev,
                             const float* unary, const float* m, float* out, int N, int K,
                             hipStream_t s);
 // ragged layout: Eq. (3) into out [sum K_i] (a.in_buf[0] holds the messages),

@@ -76,6 +76,56 @@ __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2
 __device__ __forceinline__ float log2_hw(float x) { return __builtin_amdgcn_logf(x); }
 __device__ __forceinline__ float rcp_hw(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// log x = ln 2 * log2 x for a normal finite x > 0, the factor as the sum of two
+// floats (the high one truncated), and exp x = 2^(x log2 e) for -100 <= x <= 0,
+// the product as the sum of two floats whose integer part goes to the exponent.
+// Bit for bit logf and expf on these ranges (compared over every float in them);
+// without the denormal, infinity and underflow handling that the library
+// functions add (6 and 4 of about 12 instructions).
+__device__ __forceinline__ float log_normal(float x) {
+#pragma clang fp contract(off)
+    constexpr float hi = 0x1.62e42ep-1f, lo = 0x1.efa39ep-25f;
+    const float y = __builtin_amdgcn_logf(x);
+    const float e = fmaf(y, lo, fmaf(y, hi, -(y * hi)));
+    return fmaf(y, hi, e);
+}
+__device__ __forceinline__ float exp_reduced(float x) {
+#pragma clang fp contract(off)
+    constexpr float hi = 0x1.715476p+0f, lo = 0x1.4ae0bep-26f;
+    const float p = x * hi;
+    const float q = fmaf(x, lo, fmaf(x, hi, -p));
+    const float n = rintf(p);
+    return ldexpf(__builtin_amdgcn_exp2f((p - n) + q), (int)n);
+}
+// log and exp of N values per lane: the short forms when every lane of the wave
+// is in their range, else the library's.  exp: every value <= 0 (or NaN).
+template <int N>
+__device__ __forceinline__ void log_batch(float* v) {
+    float mn = v[0];
+#pragma unroll
+    for (int i = 1; i < N; ++i) mn = fminf(mn, v[i]);
+    if (__all(mn >= 1.17549435e-38f)) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = log_normal(v[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = logf(v[i]);
+    }
+}
+template <int N>
+__device__ __forceinline__ void exp_batch(float* v) {
+    float mn = v[0];
+#pragma unroll
+    for (int i = 1; i < N; ++i) mn = fminf(mn, v[i]);
+    if (__all(mn >= -100.0f)) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = exp_reduced(v[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = expf(v[i]);
+    }
+}
+
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -93,6 +143,42 @@ __device__ __forceinline__ void lds_barrier() {
     __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Wave reductions on the vector units: lane 63 collects the wave through DPP row
+// shifts and row broadcasts, six dependent instructions instead of six trips
+// through the LDS crossbar (ds_bpermute).  A lane without a source adds `id`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned int dpp_or(unsigned int id, unsigned int v) {
+    return (unsigned int)__builtin_amdgcn_update_dpp((int)id, (int)v, CTRL, ROWS, 0xF, false);
+}
+constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118;
+constexpr int kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+// Sum over the wave, valid in lane 63.
+__device__ __forceinline__ unsigned int dpp_sum_last(unsigned int v) {
+    v += dpp_or<kRowShr1, 0xF>(0u, v);
+    v += dpp_or<kRowShr2, 0xF>(0u, v);
+    v += dpp_or<kRowShr4, 0xF>(0u, v);
+    v += dpp_or<kRowShr8, 0xF>(0u, v);
+    v += dpp_or<kRowBcast15, 0xA>(0u, v);
+    v += dpp_or<kRowBcast31, 0xC>(0u, v);
+    return v;
+}
+__device__ __forceinline__ unsigned int dpp_max_last(unsigned int v) {
+    v = max(v, dpp_or<kRowShr1, 0xF>(0u, v));
+    v = max(v, dpp_or<kRowShr2, 0xF>(0u, v));
+    v = max(v, dpp_or<kRowShr4, 0xF>(0u, v));
+    v = max(v, dpp_or<kRowShr8, 0xF>(0u, v));
+    v = max(v, dpp_or<kRowBcast15, 0xA>(0u, v));
+    v = max(v, dpp_or<kRowBcast31, 0xC>(0u, v));
+    return v;
+}
+// The same, in every lane (a scalar).
+__device__ __forceinline__ unsigned int wave_sum32(unsigned int v) {
+    return (unsigned int)__builtin_amdgcn_readlane((int)dpp_sum_last(v), 63);
+}
+__device__ __forceinline__ unsigned int wave_max32(unsigned int v) {
+    return (unsigned int)__builtin_amdgcn_readlane((int)dpp_max_last(v), 63);
+}
+
 struct RedScratch {
     float rmax[kBlock / 64];
     unsigned int act[kBlock / 64];
@@ -107,16 +193,14 @@ struct RedScratch {
 __device__ __forceinline__ void block_accumulate(RedScratch* red, CounterLine* ctr, unsigned int t,
                                                  float rmax, unsigned int act, unsigned int sa,
                                                  unsigned int sb) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        rmax = fmaxf(rmax, __shfl_xor(rmax, o, 64));
-        act += __shfl_xor(act, o, 64);
-        sa += __shfl_xor(sa, o, 64);
-        sb += __shfl_xor(sb, o, 64);
-    }
+    // (residuals are non-negative, so their bit patterns order as integers)
+    const unsigned int rm = dpp_max_last(__float_as_uint(rmax));
+    act = dpp_sum_last(act);
+    sa = dpp_sum_last(sa);
+    sb = dpp_sum_last(sb);
     const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        red->rmax[w] = rmax;
+    if ((threadIdx.x & 63) == 63) {
+        red->rmax[w] = __uint_as_float(rm);
         red->act[w] = act;
         red->sa[w] = sa;
         red->sb[w] = sb;
@@ -146,18 +230,6 @@ __device__ __forceinline__ int tile_of_block(const EvalArgs& a) {
     return (b & 7) * a.tiles_per_xcd + (b >> 3);
 }
 
-__device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-__device__ __forceinline__ unsigned int wave_max32(unsigned int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (unsigned int)__shfl_xor((int)v, o, 64));
-    return v;
-}
-
 // Which of the two committed outcomes iteration t - 1 kept: p_{t-1} is the low
 // setting when EdgeRatio = n_{t-1} / n_{t-2} exceeds the threshold (Sec. IV-A).
 __device__ __forceinline__ int select_outcome(const EvalArgs& a, unsigned long long n1, long long n2) {
@@ -170,18 +242,17 @@ __device__ __forceinline__ int select_outcome(const EvalArgs& a, unsigned long l
 // (lane c reads copy c): n of iterations t - 1 and t - 2, and for the block that
 // closes iteration t - 1 also its frontier sizes and max residual.
 struct CtrLoad {
-    unsigned long long n1, n2, sa, sb;
-    unsigned int rm, done;
+    unsigned int n1, n2, sa, sb, rm, done;
 };
 
 __device__ __forceinline__ void ctr_load(const EvalArgs& a, bool lead, CtrLoad& c) {
     const int lane = threadIdx.x & 63;
     const CounterLine* c1 = a.ctr + ((a.t - 1u) & 3u) * kCounterCopies + lane;
     c.done = a.st->done;
-    c.n1 = c1->active;
-    c.n2 = a.it >= 2 ? a.ctr[((a.t - 2u) & 3u) * kCounterCopies + lane].active : 0ull;
-    c.sa = lead ? c1->sel_a : 0ull;
-    c.sb = lead ? c1->sel_b : 0ull;
+    c.n1 = (unsigned int)c1->active;
+    c.n2 = a.it >= 2 ? (unsigned int)a.ctr[((a.t - 2u) & 3u) * kCounterCopies + lane].active : 0u;
+    c.sa = lead ? (unsigned int)c1->sel_a : 0u;
+    c.sb = lead ? (unsigned int)c1->sel_b : 0u;
     c.rm = lead ? c1->rmax : 0u;
 }
 
@@ -194,14 +265,15 @@ __device__ __forceinline__ void ctr_load(const EvalArgs& a, bool lead, CtrLoad& 
 __device__ void wave_close(const EvalArgs& a, bool close, const CtrLoad& c,
                            unsigned long long& n1_out, long long& n2_out) {
     const int lane = threadIdx.x & 63;
-    const unsigned long long n1 = wave_sum64(c.n1);
-    const unsigned long long n2 = wave_sum64(c.n2);
+    // (counts of a launch are at most the number of messages, below 2^31)
+    const unsigned long long n1 = wave_sum32(c.n1);
+    const unsigned long long n2 = wave_sum32(c.n2);
     const long long n2s = a.it >= 2 ? (long long)n2 : a.prev_active_host;
     n1_out = n1;
     n2_out = n2s;
     if (!close) return;
-    const unsigned long long sa = wave_sum64(c.sa);
-    const unsigned long long sb = wave_sum64(c.sb);
+    const unsigned long long sa = wave_sum32(c.sa);
+    const unsigned long long sb = wave_sum32(c.sb);
     const unsigned int rm = wave_max32(c.rm);
     CounterLine* z = a.ctr + ((a.t + 1u) & 3u) * kCounterCopies + lane;
     z->active = 0ull;
@@ -903,7 +975,8 @@ __device__ __forceinline__ void slot_update_split(const EvalArgs& a, const FlagR
     }
     mx = group_max<R>(mx);
 #pragma unroll
-    for (int i = 0; i < KR; ++i) gp[i] = expf(gp[i] - mx);
+    for (int i = 0; i < KR; ++i) gp[i] -= mx;
+    exp_batch<KR>(gp);
     const float* tab =
         a.pair_kind == kPairSharedAsym && a.orient[s] ? s_psiT : s_psi;
     float c[KR];
@@ -1042,35 +1115,50 @@ __device__ __forceinline__ void mfma32_table(const EvalArgs& a, float* pb) {
     for (int st = 0; st < 16; ++st) pb[st] = a.pair[mfma32_state<BF16>(st, h) * 32 + m];
 }
 
-// old: the lane's 16 states of its slot's current row (issued by the caller).
+// Position of state x in an LDS row of k_eval_mfma32: the 16 states of half h
+// (mfma32_state) are consecutive at 16 h, so a lane reads its operands as four
+// 16-byte words.
+constexpr int kMfmaStride = 36;  // floats per row: 16-byte aligned, 8 rows span the 32 banks
+
 // p_out (row_flags): the outcome whose rows are written whole.
 template <int MODE, bool BF16 = false>
-__device__ __forceinline__ void slot_update_mfma32(const EvalArgs& a, const float* pb,
-                                                   const float* old, float* s_logm,
-                                                   const float* s_A,
-                                                   const unsigned short* s_owner, int s0,
-                                                   int n0, int ns, float& rmax,
-                                                   unsigned int& act, unsigned int& sa,
-                                                   unsigned int& sb, int p_out = 0) {
-    constexpr int K = 32, KS = 33;
+__device__ __forceinline__ void slot_update_mfma32(const EvalArgs& a, const FlagRows& fr,
+                                                   float* s_logm, const float* s_A,
+                                                   const unsigned short* s_owner,
+                                                   const int* s_ptr, int s0, int n0, int ns,
+                                                   float& rmax, unsigned int& act,
+                                                   unsigned int& sa, unsigned int& sb, int p_out) {
+    constexpr int K = 32, KS = kMfmaStride;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int m = lane & 31, h = lane >> 5;
     const int q = 32 * w + m;  // slot of the tile
     const bool valid = q < ns;
-    auto state = [&](int st) { return mfma32_state<BF16>(st, h); };
     // A operand: the cavity distribution of slot q at the lane's states
     const int v = valid ? s_owner[q] : 0;
     float gv[16];
     float mx = -3.402823466e38f;
 #pragma unroll
-    for (int st = 0; st < 16; ++st) {
-        const int x = state(st);
-        gv[st] = valid ? s_A[v * KS + x] - s_logm[q * KS + x] : 0.0f;
-        mx = fmaxf(mx, gv[st]);
+    for (int t4 = 0; t4 < 4; ++t4) {
+        const float4 A4 = *(const float4*)(s_A + v * KS + 16 * h + 4 * t4);
+        const float4 l4 = *(const float4*)(s_logm + q * KS + 16 * h + 4 * t4);
+        // (nothing reads the product of a row past the tile's slots)
+        gv[4 * t4] = A4.x - l4.x;
+        gv[4 * t4 + 1] = A4.y - l4.y;
+        gv[4 * t4 + 2] = A4.z - l4.z;
+        gv[4 * t4 + 3] = A4.w - l4.w;
     }
+#pragma unroll
+    for (int st = 0; st < 16; ++st) mx = fmaxf(mx, gv[st]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
 #pragma unroll
-    for (int st = 0; st < 16; ++st) gv[st] = expf(gv[st] - mx);
+    for (int st = 0; st < 16; ++st) gv[st] -= mx;
+    exp_batch<16>(gv);
+    // (held back, here and for the lane's own row below, so that the registers of
+    // one phase are not live through the others: 56 instead of 123, and LDS, not
+    // registers, sets the resident blocks)
+    __builtin_amdgcn_sched_barrier(0);
+    float pb[16];
+    mfma32_table<BF16>(a, pb);
     floatx16 d;
 #pragma unroll
     for (int r = 0; r < 16; ++r) d[r] = 0.0f;
@@ -1088,6 +1176,20 @@ __device__ __forceinline__ void slot_update_mfma32(const EvalArgs& a, const floa
         for (int st = 0; st < 16; ++st)
             d = __builtin_amdgcn_mfma_f32_32x32x2f32(gv[st], pb[st], d, 0, 0, 0);
     }
+    __builtin_amdgcn_sched_barrier(0);
+    // the lane's own row: states 16 h .. of slot m (after the product, so that
+    // its registers are not held through it; requested before the LDS round trip)
+    const int sl = s0 + q;
+    const long long eo = (long long)min(sl, s0 + ns - 1) * K + 16 * h;
+    float old[16];
+#pragma unroll
+    for (int t4 = 0; t4 < 4; ++t4) {
+        const float4 o4 = *(const float4*)(fr.p + eo + 4 * t4);
+        old[4 * t4] = o4.x;
+        old[4 * t4 + 1] = o4.y;
+        old[4 * t4 + 2] = o4.z;
+        old[4 * t4 + 3] = o4.w;
+    }
     // D[i][m] -> LDS row 32 w + i (the wave's own rows of the log buffer, which
     // its lanes have finished reading: LDS operations of a wave run in order)
     float* rows = s_logm + (32 * w) * KS;
@@ -1096,16 +1198,34 @@ __device__ __forceinline__ void slot_update_mfma32(const EvalArgs& a, const floa
     // back as slot m, states 16 h .. 16 h + 15
     float c[16];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) c[t] = rows[m * KS + 16 * h + t];
+    for (int t4 = 0; t4 < 4; ++t4) {
+        const float4 c4 = *(const float4*)(rows + m * KS + 16 * h + 4 * t4);
+        c[4 * t4] = c4.x;
+        c[4 * t4 + 1] = c4.y;
+        c[4 * t4 + 2] = c4.z;
+        c[4 * t4 + 3] = c4.w;
+    }
     if (!valid) return;
+    if (fr.on) {
+        // the flag is the sign of the row's first entry (lane h = 0 holds it)
+        if (fr.alt && __shfl((int)(__float_as_uint(old[0]) >> 31), m, 64)) {
+#pragma unroll
+            for (int t4 = 0; t4 < 4; ++t4) {
+                const float4 o4 = *(const float4*)(fr.alt + eo + 4 * t4);
+                old[4 * t4] = o4.x;
+                old[4 * t4 + 1] = o4.y;
+                old[4 * t4 + 2] = o4.z;
+                old[4 * t4 + 3] = o4.w;
+            }
+        }
+        if (h == 0) old[0] = fabsf(old[0]);
+    }
     float z = 0.0f;
 #pragma unroll
     for (int t = 0; t < 16; ++t) z += c[t];
     const float zo = __shfl_xor(z, 32, 64);
     z = h == 0 ? z + zo : zo + z;
     const float inv = 1.0f / z;
-    const int sl = s0 + q;
-    const long long eo = (long long)sl * K + 16 * h;
     float r = 0.0f;
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
@@ -1126,7 +1246,7 @@ __device__ __forceinline__ void slot_update_mfma32(const EvalArgs& a, const floa
         bool ka = false, kb = false;
         if (active) {
             const int node = n0 + v;
-            const unsigned int u24 = draw24(a, node, sl - a.node_ptr[node]);
+            const unsigned int u24 = draw24(a, node, q - s_ptr[v]);
             ka = u24 < a.thr_a;
             kb = u24 < a.thr_b;
         }
@@ -1192,8 +1312,6 @@ __device__ __forceinline__ void matvec_uniform(ConstF P, const float* g, float* 
     }
 }
 
-// EXACT: K == KP, so K is a compile-time constant (shifts instead of
-// divisions, scalar loads of a shared table).
 // LDS of the [E][K] kernels: rows of K + 1 floats (a thread per slot reads its
 // own row, and an odd stride puts the rows of neighbouring lanes in different
 // banks).  Node rows are sized by the largest node count of a tile.
@@ -1268,11 +1386,15 @@ __device__ __forceinline__ void generic_phase1(const EvalArgs& a, const float* _
             if (f[j]) gat[j] = m_alt[(long long)l.rev[q] * K + x];
         }
     }
+    // (the flag bit is the sign of a row's first entry; messages are non-negative)
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) gat[j] = fK * fabsf(gat[j]);
+    log_batch<kPer>(gat);
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
         const int i = tid + j * kBlock;
         const int q = i / K, x = i - q * K;
-        if (q < ns) l.logm[q * KS + x] = logf(fK * (x == 0 ? fabsf(gat[j]) : gat[j]));
+        if (q < ns) l.logm[q * KS + x] = gat[j];
     }
     // the nodes' unaries (loads first), then the aggregates
 #pragma unroll
@@ -1301,95 +1423,178 @@ __device__ __forceinline__ void generic_phase1(const EvalArgs& a, const float* _
 // K = 32 with a symmetric shared table and no oversized node: Eq. (2) on the
 // matrix cores (slot_update_mfma32).  A kernel of its own, so that its register
 // count (and hence its occupancy) is not set by the paths it does not take.
-// A block per tile; the table columns and the lane's own row are loaded at the
-// start, so that they arrive while the incoming rows are gathered and
-// aggregated.  (A persistent variant that pipelined several tiles per block
-// ran slower: its register and LDS footprint halved the resident blocks.)
-// Five waves per SIMD (96 registers, one spilled) instead of the four that the
-// unconstrained allocation (115 with the accumulators) leaves: the kernel is
-// bound by memory latency, so more resident waves hide more of it.
+//
+// What bounds it is latency: a tile is a chain of dependent loads (counters ->
+// buffer choice; tile bounds -> reverse slots -> incoming rows), and a CU holds a
+// handful of blocks.  So the counters, the tile's bounds, reverse slots and node
+// bounds are requested together, then the incoming rows, the lane's own row and
+// the unaries; only LDS barriers separate the phases, so no request is waited
+// for before its value is used.  (Several tiles per block, the next one's
+// constants prefetched, ran slower: 949 and 1,003 us a solve for three and six
+// tiles against 935 for one.)
+struct Mfma32Lds {
+    float* logm;             // [128][kMfmaStride]
+    float* A;                // [TN][kMfmaStride]
+    int* rev;                // [128]
+    int* ptr;                // [TN + 1]
+    unsigned short* owner;   // [128]
+};
+constexpr int kMfmaSlots = kTileFloatsGeneric / 32;
+__host__ __device__ inline size_t mfma32_lds_bytes(int TN) {
+    return sizeof(float) * (size_t)kMfmaStride * (kMfmaSlots + TN) +
+           sizeof(int) * (size_t)(kMfmaSlots + TN + 1) + sizeof(unsigned short) * kMfmaSlots;
+}
+
 template <int MODE, bool BF16>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_eval_mfma32(
+__global__ __launch_bounds__(kBlock) void k_eval_mfma32(
     EvalArgs a) {
+    extern __shared__ float4 smem4[];
+    __shared__ RedScratch red;
+    __shared__ unsigned long long s_red[2];
+    constexpr int K = 32, KS = kMfmaStride;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int TN = a.tile_nodes_max;
+    Mfma32Lds l;
+    l.logm = (float*)smem4;
+    l.A = l.logm + kMfmaSlots * KS;
+    l.rev = (int*)(l.A + TN * KS);
+    l.ptr = l.rev + kMfmaSlots;
+    l.owner = (unsigned short*)(l.ptr + TN + 1);
+
+    CtrLoad cl;
+    prologue_issue(a, cl, blockIdx.x == 0);
+    const int tile = tile_of_block(a);
+    const bool has = tile < a.num_tiles;
+    const int n0 = has ? a.tile_start[tile] : 0, n1 = has ? a.tile_start[tile + 1] : 0;
+    const int s0 = has ? a.tile_slot[tile] : 0, s1 = has ? a.tile_slot[tile + 1] : 0;
+    const int nn = n1 - n0, ns = s1 - s0;
+    // (a tile without slots reads row 0 and uses nothing of it)
+    if (tid < max(ns, 1)) l.rev[tid] = ns > 0 ? a.rev[s0 + tid] : 0;
+    if (tid <= nn && has) l.ptr[tid] = a.node_ptr[n0 + tid] - s0;
+    const float* m_sel = prologue_finish(a, cl, s_red, blockIdx.x == 0);
+    if (!m_sel || !has) return;
+    int p_out;
+    const FlagRows fr = flag_inputs(a, m_sel, p_out);
+    const float* __restrict__ m_in = fr.p;
+    float rmax = 0.0f;
+    unsigned int act = 0, sa = 0, sb = 0;
+    lds_barrier();
+    // incoming rows: eight lanes per row, four rows per thread
+    float4 g4[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int i = tid + u * kBlock, q = i >> 3;
+        g4[u] = *(const float4*)(m_in + (long long)l.rev[min(q, max(ns - 1, 0))] * K +
+                                 4 * (i & 7));
+    }
+    // unaries of node v (this thread's four positions p4 ..)
+    auto load_unary = [&](int v, int p4) {
+        const float* un = a.unary + (long long)(n0 + min(v, max(nn - 1, 0))) * K;
+        const int h = p4 >> 4, st = p4 & 15;
+        return make_float4(un[mfma32_state<BF16>(st, h)], un[mfma32_state<BF16>(st + 1, h)],
+                           un[mfma32_state<BF16>(st + 2, h)], un[mfma32_state<BF16>(st + 3, h)]);
+    };
+    float4 acc = load_unary(tid >> 3, 4 * (tid & 7));
+    if (fr.alt) {
+        // the other outcome was chosen: flagged rows (the sign of a row's
+        // first entry) come from alt
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = tid + u * kBlock, q = i >> 3;
+            const int f = __shfl((int)(__float_as_uint(g4[u].x) >> 31), lane & ~7, 64);
+            if (f && q < ns)
+                g4[u] = *(const float4*)(fr.alt + (long long)l.rev[q] * K + 4 * (i & 7));
+        }
+    }
+    // logs of K m (as generic_phase1)
+    constexpr float fK = (float)K;
+    float lg[16];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        lg[4 * u] = fK * fabsf(g4[u].x);
+        lg[4 * u + 1] = fK * g4[u].y;
+        lg[4 * u + 2] = fK * g4[u].z;
+        lg[4 * u + 3] = fK * g4[u].w;
+    }
+    log_batch<16>(lg);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int i = tid + u * kBlock, q = i >> 3, x4 = i & 7;
+        float* row = l.logm + q * KS;
+        if (BF16) {
+            *(float4*)(row + 16 * (x4 & 1) + 4 * (x4 >> 1)) =
+                make_float4(lg[4 * u], lg[4 * u + 1], lg[4 * u + 2], lg[4 * u + 3]);
+        } else {
+            *(float2*)(row + 2 * x4) = make_float2(lg[4 * u], lg[4 * u + 2]);
+            *(float2*)(row + 16 + 2 * x4) = make_float2(lg[4 * u + 1], lg[4 * u + 3]);
+        }
+    }
+    // node aggregates: a thread per node and four positions
+    for (int i0 = 0; i0 < 8 * nn; i0 += kBlock) {
+        const int i = i0 + tid, v = i >> 3, p4 = 4 * (i & 7);
+        if (i0) acc = load_unary(v, p4);
+        if (i0 == 0) lds_barrier();  // the logs are in LDS
+        if (v < nn) {
+            const int q0 = l.ptr[v], q1 = l.ptr[v + 1];
+            for (int q = q0; q < q1; ++q) {
+                const float4 t = *(const float4*)(l.logm + q * KS + p4);
+                acc.x += t.x;
+                acc.y += t.y;
+                acc.z += t.z;
+                acc.w += t.w;
+                if (p4 == 0) l.owner[q] = (unsigned short)v;
+            }
+            *(float4*)(l.A + v * KS + p4) = acc;
+        }
+    }
+    lds_barrier();
+    slot_update_mfma32<MODE, BF16>(a, fr, l.logm, l.A, l.owner, l.ptr, s0, n0, ns, rmax, act, sa, sb,
+                                   p_out);
+    block_accumulate(&red, a.ctr, a.t, rmax, act, sa, sb);
+}
+
+// Shared tables with K = 32 or 64: each slot is split over R = 2 or 4 lanes,
+// which read the table from LDS (the lanes of a wave need different columns).
+// Graphs with a node over the tile limit take k_eval_pairs.
+template <int KP, int MODE>
+__global__ __launch_bounds__(kBlock) void k_eval_split(EvalArgs a) {
     extern __shared__ float smem[];
     __shared__ RedScratch red;
     __shared__ unsigned long long s_red[2];
     const float* m_sel = iteration_prologue(a, s_red, blockIdx.x == 0);
     if (!m_sel) return;
-    const int tile = tile_of_block(a);
-    if (tile >= a.num_tiles) return;
-    constexpr int K = 32;
-    constexpr int TS = kTileFloatsGeneric / K;
-    const GenericLds l = generic_lds(smem, K, TS, a.tile_nodes_max, 0);
     int p_out;
     const FlagRows fr = flag_inputs(a, m_sel, p_out);
-    const bool flagged_in = fr.on != 0;
-    const float* __restrict__ m_in = fr.p;
-    const float* m_alt = fr.alt;
+    const int tile = tile_of_block(a);
+    if (tile >= a.num_tiles) return;
+    constexpr int TS = kTileFloatsGeneric / KP;  // slots per tile
+    constexpr int R = KP * kBlock / kTileFloatsGeneric;
+    static_assert(R == 2 || R == 4, "lane groups of 2 or 4");
+    const bool asym = a.pair_kind == kPairSharedAsym;
+    const GenericLds l = generic_lds(smem, KP, TS, a.tile_nodes_max, asym ? 2 : 1);
     const int n0 = a.tile_start[tile], n1 = a.tile_start[tile + 1];
     const int s0 = a.tile_slot[tile], s1 = a.tile_slot[tile + 1];
-    const int ns = s1 - s0;
-    float pb[16];
-    mfma32_table<BF16>(a, pb);
-    float old[16];
-    {
-        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-        const int q = 32 * w + (lane & 31);
-        const long long eo = (long long)(s0 + min(q, max(ns - 1, 0))) * K + 16 * (lane >> 5);
-#pragma unroll
-        for (int t4 = 0; t4 < 4; ++t4) {
-            const float4 o4 = *(const float4*)(m_in + eo + 4 * t4);
-            old[4 * t4] = o4.x;
-            old[4 * t4 + 1] = o4.y;
-            old[4 * t4 + 2] = o4.z;
-            old[4 * t4 + 3] = o4.w;
-        }
-        if (flagged_in) {
-            // the flag is the sign of entry 0, held by the lane with h = 0
-            const unsigned int f0 = __float_as_uint(old[0]) >> 31;
-            const unsigned int f = (unsigned int)__shfl((int)f0, lane & 31, 64);
-            if (m_alt && f) {
-#pragma unroll
-                for (int t4 = 0; t4 < 4; ++t4) {
-                    const float4 o4 = *(const float4*)(m_alt + eo + 4 * t4);
-                    old[4 * t4] = o4.x;
-                    old[4 * t4 + 1] = o4.y;
-                    old[4 * t4 + 2] = o4.z;
-                    old[4 * t4 + 3] = o4.w;
-                }
-            }
-            if ((lane >> 5) == 0) old[0] = fabsf(old[0]);
-        }
-    }
-    generic_phase1(a, m_in, l, K, n0, n1 - n0, s0, ns, m_alt);
+    const int ns = s1 - s0, nn = n1 - n0;
+    for (int i = threadIdx.x; i < KP * KP; i += kBlock) l.psi[i] = a.pair[i];
+    if (asym)
+        for (int i = threadIdx.x; i < KP * KP; i += kBlock) l.psiT[i] = a.pair[(i % KP) * KP + i / KP];
+    generic_phase1(a, fr.p, l, KP, n0, nn, s0, ns, fr.alt);
     float rmax = 0.0f;
     unsigned int act = 0, sa = 0, sb = 0;
-    slot_update_mfma32<MODE, BF16>(a, pb, old, l.logm, l.A, l.owner, s0, n0, ns, rmax, act, sa,
-                                   sb, p_out);
+    slot_update_split<KP, R, MODE>(a, fr, l.logm, l.A, l.psi, l.psiT, l.owner, s0, n0, ns, rmax, act,
+                                   sa, sb, p_out);
     block_accumulate(&red, a.ctr, a.t, rmax, act, sa, sb);
 }
 
-// Waves per SIMD asked of the register allocator for k_eval_generic<KP, MODE,
-// EXACT> (1 leaves it unconstrained).  The kernel waits on memory, so more
-// resident waves pay for a spilled register or two: K = 8 and 32 take five
-// (96 registers; 99 and 114 unconstrained), K = 64 takes three (168; 170) and
-// under RnBP, whose second outcome needs more live values, or with K below the
-// width, two (256; unconstrained the allocator spills into the accumulation
-// registers and leaves one).  The other widths fit without a cap, and so does
-// the lane-group instantiation (SPLIT: about 60 registers, LDS sets its
-// occupancy).
-template <int KP, int MODE, bool EXACT, bool SPLIT>
-constexpr int generic_waves() {
-    if (SPLIT) return 1;
-    if (KP == 64) return EXACT && MODE != 1 ? 3 : 2;
-    return (KP == 8 || KP == 32) && EXACT ? 5 : 1;
-}
-
-// SPLIT: the launch guarantees a shared table, K == KP with R > 1 and no tile
-// holding a node over its slot limit, so only the lane-group path is compiled
-// (its registers are then not those of the per-slot path).
-template <int KP, int MODE, bool EXACT, bool SPLIT = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(generic_waves<KP, MODE, EXACT, SPLIT>())))
+// K up to 16 (shared tables; K = 2 also Ising and per-slot tables): a thread per
+// slot, every K compiled, so that the products are K * K multiply-adds that take
+// the table from scalar registers.  (One width per power of two, the states past
+// K predicated away, took 428 us for ten RnBP sweeps of a 300 x 300 grid with
+// K = 5 and 616 us for nine LBP sweeps with K = 13.)  K = 8 asks the register
+// allocator for five waves per SIMD (96 registers; 99 unconstrained): the kernel
+// waits on memory, so more resident waves pay for a spilled register or two.
+template <int KP, int MODE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(KP == 8 ? 5 : 1)))
 void k_eval_generic(EvalArgs a) {
     extern __shared__ float smem[];
     __shared__ RedScratch red;
@@ -1401,32 +1606,21 @@ void k_eval_generic(EvalArgs a) {
     const float* __restrict__ m_in = fr.p;
     const int tile = tile_of_block(a);
     if (tile >= a.num_tiles) return;
-    const int K = EXACT ? KP : a.num_states;
+    constexpr int K = KP;
     const int TS = kTileFloatsGeneric / K;  // slots per tile
     const int KS = K + 1;
-    const GenericLds l =
-        generic_lds(smem, K, TS, a.tile_nodes_max, a.pair_kind == kPairSharedAsym ? 2 : 1);
+    const GenericLds l = generic_lds(smem, K, TS, a.tile_nodes_max, 0);
     float* s_logm = l.logm;
     float* s_A = l.A;
-    float* s_psi = l.psi;
     unsigned short* s_owner = l.owner;
 
     const int n0 = a.tile_start[tile], n1 = a.tile_start[tile + 1];
     const int s0 = a.tile_slot[tile], s1 = a.tile_slot[tile + 1];
     const int ns = s1 - s0, nn = n1 - n0;
     const int tid = threadIdx.x;
-    const bool big = !SPLIT && ns > TS;
+    const bool big = ns > TS;
     const float fK = (float)K;
 
-    // K > 16 with a shared table: each slot is split over R lanes, which read
-    // the table from LDS (the lanes of a wave need different columns)
-    constexpr int R = (EXACT && KP * kBlock > kTileFloatsGeneric) ? KP * kBlock / kTileFloatsGeneric : 1;
-    static_assert(!SPLIT || R > 1, "the lane-group path needs K = KP > 16");
-    const bool shared = SPLIT || a.pair_kind == kPairShared || a.pair_kind == kPairSharedAsym;
-    if (shared && (!EXACT || R > 1))
-        for (int i = tid; i < K * K; i += kBlock) s_psi[i] = a.pair[i];
-    if (R > 1 && a.pair_kind == kPairSharedAsym)
-        for (int i = tid; i < K * K; i += kBlock) l.psiT[i] = a.pair[(i % K) * K + i / K];
     if (!big) {
         generic_phase1(a, m_in, l, K, n0, nn, s0, ns, fr.alt);
     } else {
@@ -1451,12 +1645,6 @@ void k_eval_generic(EvalArgs a) {
 
     float rmax = 0.0f;
     unsigned int act = 0, sa = 0, sb = 0;
-    if (R > 1 && shared && !big) {
-        slot_update_split<KP, R, MODE>(a, fr, s_logm, s_A, s_psi, l.psiT, s_owner, s0, n0, ns, rmax, act,
-                                       sa, sb, p_out);
-        block_accumulate(&red, a.ctr, a.t, rmax, act, sa, sb);
-        return;
-    }
     for (int q = tid; q < ns; q += kBlock) {
         const int s = s0 + q;
         const int v = big ? 0 : s_owner[q];
@@ -1466,15 +1654,13 @@ void k_eval_generic(EvalArgs a) {
         float mx = -3.402823466e38f;
 #pragma unroll
         for (int x = 0; x < KP; ++x) {
-            if (x < K) {
-                const float lm = big ? logf(fK * flag_entry(fr, rin, x)) : s_logm[q * KS + x];
-                g[x] = s_A[v * KS + x] - lm;
-                mx = fmaxf(mx, g[x]);
-            }
+            const float lm = big ? logf(fK * flag_entry(fr, rin, x)) : s_logm[q * KS + x];
+            g[x] = s_A[v * KS + x] - lm;
+            mx = fmaxf(mx, g[x]);
         }
 #pragma unroll
-        for (int x = 0; x < KP; ++x)
-            if (x < K) g[x] = expf(g[x] - mx);
+        for (int x = 0; x < KP; ++x) g[x] -= mx;
+        exp_batch<KP>(g);
         float c[KP];
 #pragma unroll
         for (int y = 0; y < KP; ++y) c[y] = 0.0f;
@@ -1484,59 +1670,39 @@ void k_eval_generic(EvalArgs a) {
             const float ep = expf(J - fabsf(J)), em = expf(-J - fabsf(J));
             c[0] = ep * g[0] + em * g[1];
             c[1] = em * g[0] + ep * g[1];
-        } else if (EXACT && a.pair_kind != kPairDense) {
+        } else if (a.pair_kind != kPairDense) {
             const ConstF P4 = (ConstF)(uintptr_t)a.pair;
             if (a.pair_kind == kPairSharedAsym && a.orient[s])
                 matvec_uniform<KP, true>(P4, g, c);
             else
                 matvec_uniform<KP, false>(P4, g, c);
         } else {
-            // c(y) = sum_x psi(x, y) g(x): element (x, y) of the table at
-            // P[x * sx + y * sy] (the transpose for the other direction)
-            const float* P;
-            int sx = K, sy = 1;
-            if (a.pair_kind == kPairDense) {
-                P = a.pair + (long long)s * K * K;
-            } else {
-                P = s_psi;
-                if (a.pair_kind == kPairSharedAsym && a.orient[s]) {
-                    sx = 1;
-                    sy = K;
-                }
-            }
+            // per-slot tables (K = 2 only; wider ones take k_eval_pairs)
+            const float* P = a.pair + (long long)s * K * K;
 #pragma unroll
-            for (int x = 0; x < KP; ++x) {
-                if (x < K) {
-                    const float gx = g[x];
+            for (int x = 0; x < K; ++x)
 #pragma unroll
-                    for (int y = 0; y < KP; ++y)
-                        if (y < K) c[y] = fmaf(P[x * sx + y * sy], gx, c[y]);
-                }
-            }
+                for (int y = 0; y < K; ++y) c[y] = fmaf(P[x * K + y], g[x], c[y]);
         }
         float z = 0.0f;
 #pragma unroll
-        for (int y = 0; y < KP; ++y)
-            if (y < K) z += c[y];
+        for (int y = 0; y < KP; ++y) z += c[y];
         const float inv = 1.0f / z;
         const long long eo = (long long)s * K;
         float r = 0.0f;
         float old[KP];
 #pragma unroll
         for (int y = 0; y < KP; ++y) {
-            if (y < K) {
-                c[y] *= inv;
-                old[y] = flag_entry(fr, eo, y);
-                r = fmaxf(r, fabsf(c[y] - old[y]));
-            }
+            c[y] *= inv;
+            old[y] = flag_entry(fr, eo, y);
+            r = fmaxf(r, fabsf(c[y] - old[y]));
         }
         const bool active = r > a.eps;
         rmax = fmaxf(rmax, r);
         act += active;
         if (MODE == kModeLBP) {
 #pragma unroll
-            for (int y = 0; y < KP; ++y)
-                if (y < K) a.out_buf[0][eo + y] = c[y];
+            for (int y = 0; y < KP; ++y) a.out_buf[0][eo + y] = c[y];
         } else if (MODE == kModeRnBP) {
             bool ka = false, kb = false;
             if (active) {
@@ -1552,29 +1718,405 @@ void k_eval_generic(EvalArgs a) {
                 const bool diff = ka != kb;
                 float* op = a.out_buf[p_out] + eo;
 #pragma unroll
-                for (int y = 0; y < KP; ++y)
-                    if (y < K) op[y] = y == 0 ? flag_first(kp ? c[0] : old[0], diff) : (kp ? c[y] : old[y]);
+                for (int y = 0; y < KP; ++y) op[y] = y == 0 ? flag_first(kp ? c[0] : old[0], diff) : (kp ? c[y] : old[y]);
                 if (diff) {
                     float* os = a.out_buf[p_out ^ 1] + eo;
 #pragma unroll
-                    for (int y = 0; y < KP; ++y)
-                        if (y < K) os[y] = ko ? c[y] : old[y];
+                    for (int y = 0; y < KP; ++y) os[y] = ko ? c[y] : old[y];
                 }
             } else {
 #pragma unroll
-                for (int y = 0; y < KP; ++y)
-                    if (y < K) a.out_buf[0][eo + y] = ka ? c[y] : old[y];
+                for (int y = 0; y < KP; ++y) a.out_buf[0][eo + y] = ka ? c[y] : old[y];
                 if (a.two_outputs) {
 #pragma unroll
-                    for (int y = 0; y < KP; ++y)
-                        if (y < K) a.out_buf[1][eo + y] = kb ? c[y] : old[y];
+                    for (int y = 0; y < KP; ++y) a.out_buf[1][eo + y] = kb ? c[y] : old[y];
                 }
             }
         } else if (MODE == kModeRBP) {
 #pragma unroll
-            for (int y = 0; y < KP; ++y)
-                if (y < K) a.cand[eo + y] = c[y];
+            for (int y = 0; y < KP; ++y) a.cand[eo + y] = c[y];
             a.keys[s] = __float_as_uint(r);
+        }
+    }
+    block_accumulate(&red, a.ctr, a.t, rmax, act, sa, sb);
+}
+
+// ---------------------------------------------------------------------------
+// [E][K] layout, a lane per (slot, target state) pair: tables of their own per
+// slot (K > 2), and shared tables with a K over 16 that is not 32 or 64.
+//
+// With a thread per slot a per-slot table is read K * K floats apart by
+// neighbouring lanes, and a wide odd K needs K padded to 32 or 64 with every
+// product predicated (1,024 or 4,096 of them, unrolled).  Here the outputs of the
+// tile's slots are dealt to lanes pair by pair: consecutive lanes read
+// consecutive entries of a table row, the outputs are stored coalesced, and the
+// code does not depend on K.  Bound by the table traffic (per-slot tables) or the
+// message traffic (shared tables).  Every sum runs in the order the per-slot
+// path takes (source states and target states ascending), so both round alike.
+// Against a thread per slot, per solve: 20,000 edges with K = 21 tables of their
+// own, seven LBP sweeps, 1,166 -> 341 us; 203 x 197 Potts grid, K = 21, six LBP
+// sweeps, 763 -> 410 us; 300 x 300, K = 48, six RnBP sweeps, 10,722 -> 2,135 us.
+//
+//   1  incoming rows gathered and logged into LDS, node aggregates (as
+//      generic_phase1)
+//   2  cavity distributions g of every slot: a group of W lanes per slot (W = K
+//      rounded up to a power of two), the maximum by shuffles, g in LDS
+//   3  products c(y) = sum_x psi(x, y) g(x): per-slot tables from global memory
+//      (four pairs per lane, eight rows each in flight), shared tables from LDS,
+//      and symmetric shared tables as 32-row tiles on the matrix cores
+//      (v_mfma_f32_32x32x2f32; states past K contribute products with 0)
+//   4  a lane per slot: normalisation; pairs: |change|; a lane per slot:
+//      residual and frontier decision; pairs: stores
+// ---------------------------------------------------------------------------
+enum PairTable : int { kTabDense = 0, kTabShared = 1, kTabMfma = 2 };
+
+struct PairsLds {
+    float* G;                // [TS][KS] logs of the incoming messages, then g, then |change|
+    float* C;                // [TS][KS] outputs
+    float* A;                // [TN][KS] node aggregates
+    float* inv;              // [TS] 1 / z
+    float* psi;              // [K][K] shared table
+    int* rev;                // [TS]
+    int* ptr;                // [TN + 1]
+    unsigned int* keep;      // [TS]
+    unsigned short* owner;   // [TS]
+};
+
+__host__ __device__ inline size_t pairs_lds_bytes(int K, int TS, int TN, int tables) {
+    const int KS = K | 1;
+    return sizeof(float) * ((size_t)2 * TS * KS + (size_t)TN * KS + TS + (size_t)tables * K * K) +
+           sizeof(int) * ((size_t)TS + TN + 1 + TS) + sizeof(unsigned short) * (size_t)TS;
+}
+
+__device__ __forceinline__ PairsLds pairs_lds(float* smem, int K, int TS, int TN, int tables) {
+    const int KS = K | 1;
+    PairsLds l;
+    l.G = smem;
+    l.C = l.G + TS * KS;
+    l.A = l.C + TS * KS;
+    l.inv = l.A + TN * KS;
+    l.psi = l.inv + TS;
+    l.rev = (int*)(l.psi + tables * K * K);
+    l.ptr = l.rev + TS;
+    l.keep = (unsigned int*)(l.ptr + TN + 1);
+    l.owner = (unsigned short*)(l.keep + TS);
+    return l;
+}
+
+template <int MODE, int TAB>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
+    TAB == kTabShared ? 5 : 1))) void k_eval_pairs(EvalArgs a) {
+    extern __shared__ float smem[];
+    __shared__ RedScratch red;
+    __shared__ unsigned long long s_red[2];
+    constexpr int U = TAB == kTabMfma ? 8 : 4;  // pairs per lane in flight
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int K = a.num_states, KS = K | 1;
+    const int TS = a.tile_slots_max, TN = a.tile_nodes_max;
+    const PairsLds l = pairs_lds(smem, K, TS, TN, TAB == kTabDense ? 0 : 1);
+    const unsigned int magic = a.k_magic;
+    auto row_of = [&](int i) { return (int)(((unsigned int)i * magic) >> 20); };  // i / K
+    // the counters and the tile's graph constants are in flight together
+    CtrLoad cl;
+    prologue_issue(a, cl, blockIdx.x == 0);
+    const int tile = tile_of_block(a);
+    const bool has = tile < a.num_tiles;
+    const int n0 = has ? a.tile_start[tile] : 0, n1 = has ? a.tile_start[tile + 1] : 0;
+    const int s0 = has ? a.tile_slot[tile] : 0, s1 = has ? a.tile_slot[tile + 1] : 0;
+    const int nn = n1 - n0, node_slots = s1 - s0;
+    // a node over the tile limit: its slots are taken TS at a time
+    const bool big = node_slots > TS;
+    const int ns0 = big ? TS : node_slots;
+    for (int q = tid; q < ns0; q += kBlock) l.rev[q] = a.rev[s0 + q];
+    for (int v = tid; v <= nn && has; v += kBlock) l.ptr[v] = a.node_ptr[n0 + v] - s0;
+    if (TAB != kTabDense) {
+        for (int i = tid; i < K * K; i += kBlock) l.psi[i] = a.pair[i];
+    }
+    const float* m_sel = prologue_finish(a, cl, s_red, blockIdx.x == 0);
+    if (!m_sel || !has) return;
+    int p_out;
+    const FlagRows fr = flag_inputs(a, m_sel, p_out);
+    const float* __restrict__ m_in = fr.p;
+    const float fK = (float)K;
+    if (big) {
+        // aggregate each state over all of the node's slots with a strided sum
+        for (int x = 0; x < K; ++x) {
+            float part = 0.0f;
+            for (int q = tid; q < node_slots; q += kBlock)
+                part += logf(fK * flag_entry(fr, (long long)a.rev[s0 + q] * K, x));
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
+            if (lane == 0) red.rmax[w] = part;
+            __syncthreads();
+            if (tid == 0) {
+                float acc = a.unary[(long long)n0 * K + x];
+                for (int i = 0; i < kBlock / 64; ++i) acc += red.rmax[i];
+                l.A[x] = acc;
+            }
+            __syncthreads();
+        }
+    }
+    __syncthreads();
+    float rmax = 0.0f;
+    unsigned int act = 0, sa = 0, sb = 0;
+    for (int base = 0; base < node_slots; base += TS) {
+        const int sc = s0 + base, ns = min(TS, node_slots - base), P = ns * K;
+        if (base) {
+            __syncthreads();  // the LDS rows of the previous slots are free
+            for (int q = tid; q < ns; q += kBlock) l.rev[q] = a.rev[sc + q];
+            __syncthreads();
+        }
+        // 1. logs of K m (as generic_phase1) and the node aggregates
+        for (int c0 = 0; c0 < P; c0 += U * kBlock) {
+            float v[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int i = c0 + tid + j * kBlock;
+                const int q = row_of(i);
+                v[j] = i < P ? m_in[(long long)l.rev[q] * K + (i - q * K)] : 1.0f;
+            }
+            if (fr.alt) {
+                // the other outcome was chosen: flagged rows come from alt
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    const int i = c0 + tid + j * kBlock;
+                    const int q = row_of(i);
+                    if (i < P) {
+                        const long long r = (long long)l.rev[q] * K;
+                        if (__float_as_uint(m_in[r]) >> 31) v[j] = fr.alt[r + (i - q * K)];
+                    }
+                }
+            }
+            // a flag is the sign of a row's first entry (messages are non-negative)
+#pragma unroll
+            for (int j = 0; j < U; ++j) v[j] = fK * fabsf(v[j]);
+            log_batch<U>(v);
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int i = c0 + tid + j * kBlock;
+                const int q = row_of(i);
+                if (i < P) l.G[q * KS + (i - q * K)] = v[j];
+            }
+        }
+        const int NK = big ? 0 : nn * K;
+        if (big)
+            for (int q = tid; q < ns; q += kBlock) l.owner[q] = 0;
+        for (int c0 = 0; c0 < NK; c0 += 4 * kBlock) {
+            float u[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int i = c0 + tid + j * kBlock;
+                u[j] = i < NK ? a.unary[(long long)n0 * K + i] : 0.0f;
+            }
+            if (c0 == 0) __syncthreads();  // the logs are in LDS
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int i = c0 + tid + j * kBlock;
+                if (i < NK) {
+                    const int v = row_of(i), x = i - v * K;
+                    const int q0 = l.ptr[v], q1 = l.ptr[v + 1];
+                    float acc = u[j];
+                    for (int q = q0; q < q1; ++q) acc += l.G[q * KS + x];
+                    l.A[v * KS + x] = acc;
+                    if (x == 0)
+                        for (int q = q0; q < q1; ++q) l.owner[q] = (unsigned short)v;
+                }
+            }
+        }
+        __syncthreads();
+
+        // 2. cavity distributions
+        {
+            const int wl = a.k_wlog, W = 1 << wl;
+            const int x = tid & (W - 1);
+            for (int q = tid >> wl; q < ns; q += kBlock >> wl) {
+                float c = -3.402823466e38f;
+                if (x < K) c = l.A[l.owner[q] * KS + x] - l.G[q * KS + x];
+                float mx = fmaxf(c, -3.402823466e38f);
+                for (int o = W >> 1; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+                if (x < K) l.G[q * KS + x] = expf(c - mx);
+            }
+        }
+        __syncthreads();
+
+        // 3. products
+        if (TAB == kTabMfma) {
+            const int m = lane & 31, h = lane >> 5;
+            for (int r0 = 32 * w; r0 < ns; r0 += 32 * (kBlock / 64)) {
+                const float* g = l.G + min(r0 + m, ns - 1) * KS;
+                for (int y0 = 0; y0 < K; y0 += 32) {
+                    const bool col = y0 + m < K;
+                    floatx16 d;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) d[r] = 0.0f;
+                    for (int xs = 0; xs < K; xs += 8) {
+                        float ga[4], pb[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int x = xs + 2 * u + h;
+                            ga[u] = x < K ? g[x] : 0.0f;
+                            pb[u] = x < K && col ? l.psi[x * K + y0 + m] : 0.0f;
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            d = __builtin_amdgcn_mfma_f32_32x32x2f32(ga[u], pb[u], d, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int q = r0 + 8 * (r >> 2) + 4 * h + (r & 3);
+                        if (q < ns && col) l.C[q * KS + y0 + m] = d[r];
+                    }
+                }
+            }
+        } else {
+            for (int c0 = 0; c0 < P; c0 += 4 * kBlock) {
+                const float* T[4];
+                const float* g[4];
+                int o[4], sx[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int i = min(c0 + tid + j * kBlock, P - 1);
+                    const int q = row_of(i), y = i - q * K;
+                    g[j] = l.G + q * KS;
+                    o[j] = q * KS + y;
+                    // element (x, y) at T[x * sx]; transposed for the other
+                    // direction of an asymmetric shared table
+                    T[j] = TAB == kTabDense ? a.pair + (long long)(sc + q) * K * K + y : l.psi + y;
+                    sx[j] = K;
+                    if (TAB == kTabShared && a.pair_kind == kPairSharedAsym && a.orient[sc + q]) {
+                        T[j] = l.psi + y * K;
+                        sx[j] = 1;
+                    }
+                }
+                float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                int x = 0;
+                for (; x + 8 <= K; x += 8) {
+                    float tv[4][8];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) tv[j][u] = T[j][(x + u) * sx[j]];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) acc[j] = fmaf(tv[j][u], g[j][x + u], acc[j]);
+                }
+                if (x < K) {
+                    // the last states in one predicated step
+                    float tv[4][8];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) tv[j][u] = x + u < K ? T[j][(x + u) * sx[j]] : 0.0f;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        if (x + u >= K) break;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) acc[j] = fmaf(tv[j][u], g[j][x + u], acc[j]);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (c0 + tid + j * kBlock < P) l.C[o[j]] = acc[j];
+            }
+        }
+        __syncthreads();
+
+        // 4. normalisation, residual, frontier decision, stores
+        for (int q = tid; q < ns; q += kBlock) {
+            const float* c = l.C + q * KS;
+            float z = 0.0f;
+            for (int y = 0; y < K; ++y) z += c[y];
+            l.inv[q] = 1.0f / z;
+        }
+        const long long e0 = (long long)sc * K;  // the tile's rows are contiguous
+        // entry i of the tile's own rows (row q)
+        auto old_entry = [&](int i, int q) {
+            float v = m_in[e0 + i];
+            if (fr.on) {
+                if (fr.alt && (__float_as_uint(m_in[e0 + q * K]) >> 31)) v = fr.alt[e0 + i];
+                v = fabsf(v);
+            }
+            return v;
+        };
+        __syncthreads();
+        for (int c0 = 0; c0 < P; c0 += U * kBlock) {
+            float old[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int i = min(c0 + tid + j * kBlock, P - 1);
+                old[j] = old_entry(i, row_of(i));
+            }
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int i = c0 + tid + j * kBlock;
+                if (i >= P) continue;
+                const int q = row_of(i), o = q * KS + (i - q * K);
+                const float v = l.C[o] * l.inv[q];
+                l.C[o] = v;
+                l.G[o] = fabsf(v - old[j]);
+            }
+        }
+        __syncthreads();
+        for (int q = tid; q < ns; q += kBlock) {
+            const float* d = l.G + q * KS;
+            float r = 0.0f;
+            for (int y = 0; y < K; ++y) r = fmaxf(r, d[y]);
+            const bool active = r > a.eps;
+            rmax = fmaxf(rmax, r);
+            act += active;
+            if (MODE == kModeRnBP) {
+                bool ka = false, kb = false;
+                if (active) {
+                    const int v = l.owner[q];
+                    const unsigned int u24 = draw24(a, n0 + v, base + q - l.ptr[v]);
+                    ka = u24 < a.thr_a;
+                    kb = u24 < a.thr_b;
+                }
+                sa += ka;
+                sb += kb;
+                l.keep[q] = (ka ? 1u : 0u) | (kb ? 2u : 0u);
+            }
+            if (MODE == kModeRBP) a.keys[sc + q] = __float_as_uint(r);
+        }
+        if (MODE == kModeRnBP) __syncthreads();
+        if (MODE != kModeEvalOnly) {
+            for (int c0 = 0; c0 < P; c0 += U * kBlock) {
+                float old[U];
+                if (MODE == kModeRnBP) {
+#pragma unroll
+                    for (int j = 0; j < U; ++j) {
+                        const int i = min(c0 + tid + j * kBlock, P - 1);
+                        old[j] = old_entry(i, row_of(i));
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    const int i = c0 + tid + j * kBlock;
+                    if (i >= P) continue;
+                    const int q = row_of(i), y = i - q * K;
+                    const float v = l.C[q * KS + y];
+                    if (MODE == kModeLBP) {
+                        a.out_buf[0][e0 + i] = v;
+                    } else if (MODE == kModeRBP) {
+                        a.cand[e0 + i] = v;
+                    } else {
+                        const unsigned int kp2 = l.keep[q];
+                        const bool ka = kp2 & 1u, kb = kp2 & 2u;
+                        if (a.row_flags) {
+                            // the whole row of outcome p_out, the other where they differ
+                            const bool kp = p_out == 0 ? ka : kb, ko = p_out == 0 ? kb : ka;
+                            const bool diff = ka != kb;
+                            const float f = kp ? v : old[j];
+                            a.out_buf[p_out][e0 + i] = y == 0 ? flag_first(f, diff) : f;
+                            if (diff) a.out_buf[p_out ^ 1][e0 + i] = ko ? v : old[j];
+                        } else {
+                            a.out_buf[0][e0 + i] = ka ? v : old[j];
+                            if (a.two_outputs) a.out_buf[1][e0 + i] = kb ? v : old[j];
+                        }
+                    }
+                }
+            }
         }
     }
     block_accumulate(&red, a.ctr, a.t, rmax, act, sa, sb);
@@ -1672,8 +2214,11 @@ __global__ void k_marginals_generic(const int* node_ptr, const int* rev, const f
                         v[u] = on && j + u < cnt ? m[(long long)ru * K + x] : 1.0f;
                     }
 #pragma unroll
+                    for (int u = 0; u < kRows; ++u) v[u] *= fK;
+                    log_batch<kRows>(v);
+#pragma unroll
                     for (int u = 0; u < kRows; ++u)
-                        if (on && j + u < cnt) acc += logf(fK * v[u]);
+                        if (on && j + u < cnt) acc += v[u];
                 }
             }
             float mx = acc;
@@ -1767,10 +2312,18 @@ __device__ __forceinline__ void ragged_slot(const EvalArgs& a, const float* __re
                 v1[j] = x1 ? m_in[rin + lane + 64] : 1.0f;
             }
 #pragma unroll
+            for (int j = 0; j < 8; ++j) v0[j] *= fK;
+            log_batch<8>(v0);
+            if (Ki > 64) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v1[j] *= fK;
+                log_batch<8>(v1);
+            }
+#pragma unroll
             for (int j = 0; j < 8; ++j) {
                 if (k0 + j >= nb) break;
-                if (x0) A0 += logf(fK * v0[j]);
-                if (x1) A1 += logf(fK * v1[j]);
+                if (x0) A0 += v0[j];
+                if (x1) A1 += v1[j];
             }
         }
     }
@@ -1934,9 +2487,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     v1[j] = x1 ? m_in[rin + lane + 64] : 1.0f;
                 }
 #pragma unroll
+                for (int j = 0; j < 8; ++j) v0[j] *= fK;
+                log_batch<8>(v0);
+                if (Ki > 64) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) v1[j] *= fK;
+                    log_batch<8>(v1);
+                }
+#pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     if (k0 + j >= deg) break;
-                    const float l0 = logf(fK * v0[j]), l1 = logf(fK * v1[j]);
+                    const float l0 = v0[j], l1 = v1[j];
                     if (x0) {
                         A0 += l0;
                         G[(k0 + j) * Ki + lane] = l0;
@@ -2240,20 +2801,21 @@ __global__ __launch_bounds__(kBlock) void k_sparse_commit(EvalArgs a) {
         const int lane = threadIdx.x;
         const unsigned int done = a.st->done;
         const CounterLine* c0 = a.ctr + (a.t & 3u) * kCounterCopies + lane;
-        const long long d = (long long)wave_sum64(c0->active);
+        // (a signed change, at most the number of messages either way: below 2^31)
+        const long long d = (int)wave_sum32((unsigned int)c0->active);
         const long long base = a.sp_first ? 0ll : (long long)a.st->sp_n[(a.t - 1u) & 3u];
         const unsigned long long n1 = (unsigned long long)(base + d);
         long long n2;
         if (!a.sp_first)
             n2 = (long long)a.st->sp_n[(a.t - 1u) & 3u];
         else if (a.it >= 1)  // switched from the full evaluation: its count of t - 1
-            n2 = (long long)wave_sum64(a.ctr[((a.t - 1u) & 3u) * kCounterCopies + lane].active);
+            n2 = (long long)wave_sum32((unsigned int)a.ctr[((a.t - 1u) & 3u) * kCounterCopies + lane].active);
         else
             n2 = a.prev_active_host;
         if (blockIdx.x == 0 && !done) {
-            const unsigned long long ev = wave_sum64(c0->sel_a);
+            const unsigned long long ev = wave_sum32((unsigned int)c0->sel_a);
             // messages committed by iteration t - 1 (none on the first sparse iteration)
-            const unsigned long long cm_prev = a.sp_first ? 0ull : wave_sum64(c0->sel_b);
+            const unsigned long long cm_prev = a.sp_first ? 0ull : wave_sum32((unsigned int)c0->sel_b);
             CounterLine* z = a.ctr + ((a.t + 2u) & 3u) * kCounterCopies + lane;
             z->active = 0ull;
             z->sel_a = 0ull;
@@ -2373,8 +2935,8 @@ constexpr int kCommitChunk = 4096;
 // IsConverged for the top-k step: nothing is selected or committed when the
 // evaluation of iteration t found no residual above eps.
 __global__ void k_rbp_gate(DevState* st, const CounterLine* ctr, int slot) {
-    const unsigned long long n = wave_sum64(ctr[slot * kCounterCopies + threadIdx.x].active);
-    if (threadIdx.x == 0) st->rbp_skip = (st->done || n == 0ull) ? 1u : 0u;
+    const unsigned int n = wave_sum32((unsigned int)ctr[slot * kCounterCopies + threadIdx.x].active);
+    if (threadIdx.x == 0) st->rbp_skip = (st->done || n == 0u) ? 1u : 0u;
 }
 
 // Keys per thread of a histogram pass and positions per thread of the tie
@@ -2488,9 +3050,9 @@ __global__ __launch_bounds__(kSelBlock) void k_rbp_scan(DevState* st, int pass, 
     __shared__ unsigned int s_skip;
     if (gate_ctr) {
         if (threadIdx.x < 64) {
-            const unsigned long long n = wave_sum64(gate_ctr[threadIdx.x].active);
+            const unsigned int n = wave_sum32((unsigned int)gate_ctr[threadIdx.x].active);
             if (threadIdx.x == 0) {
-                s_skip = (st->done || n == 0ull) ? 1u : 0u;
+                s_skip = (st->done || n == 0u) ? 1u : 0u;
                 st->rbp_skip = s_skip;
             }
         }
@@ -2698,17 +3260,17 @@ __global__ void k_sparse_rbp_close(EvalArgs a) {
     DevState* st = a.st;
     const unsigned int done = st->done;
     const CounterLine* c0 = a.ctr + (a.t & 3u) * kCounterCopies + lane;
-    const long long d = (long long)wave_sum64(c0->active);
+    const long long d = (int)wave_sum32((unsigned int)c0->active);
     const long long base = a.sp_first ? 0ll : (long long)st->sp_n[(a.t - 1u) & 3u];
     const unsigned long long n1 = (unsigned long long)(base + d);
     long long n2;
     if (!a.sp_first)
         n2 = (long long)st->sp_n[(a.t - 1u) & 3u];
     else if (a.it >= 1)  // switched from the full evaluation: its count of t - 1
-        n2 = (long long)wave_sum64(a.ctr[((a.t - 1u) & 3u) * kCounterCopies + lane].active);
+        n2 = (long long)wave_sum32((unsigned int)a.ctr[((a.t - 1u) & 3u) * kCounterCopies + lane].active);
     else
         n2 = a.prev_active_host;
-    const unsigned long long ev = wave_sum64(c0->sel_a);
+    const unsigned long long ev = wave_sum32((unsigned int)c0->sel_a);
     if (done) {
         if (lane == 0) st->rbp_skip = 1u;
         return;
@@ -2765,8 +3327,8 @@ constexpr int kRsGrid = 512;  // blocks of the grid-stride splash kernels
 // evaluation of iteration t found no residual above eps; the level lists of
 // iteration t start empty.
 __global__ void k_rs_gate(DevState* st, const CounterLine* ctr, int slot) {
-    const unsigned long long n = wave_sum64(ctr[slot * kCounterCopies + threadIdx.x].active);
-    if (threadIdx.x == 0) st->rbp_skip = (st->done || n == 0ull) ? 1u : 0u;
+    const unsigned int n = wave_sum32((unsigned int)ctr[slot * kCounterCopies + threadIdx.x].active);
+    if (threadIdx.x == 0) st->rbp_skip = (st->done || n == 0u) ? 1u : 0u;
     if (threadIdx.x <= kSplashMaxDepth) st->rs_count[threadIdx.x] = 0u;
 }
 
@@ -3037,31 +3599,41 @@ hipError_t launch_fill(float* p, float v, long long n, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int KP, bool EXACT, bool SPLIT = false>
-static hipError_t launch_generic_kp(int mode, const EvalArgs& a, int grid, size_t shm,
-                                    hipStream_t s) {
+template <int KP>
+static hipError_t launch_generic(int mode, const EvalArgs& a, int grid, size_t shm,
+                                 hipStream_t s) {
     switch (mode) {
-    case kModeLBP: k_eval_generic<KP, kModeLBP, EXACT, SPLIT><<<grid, kBlock, shm, s>>>(a); break;
-    case kModeRnBP: k_eval_generic<KP, kModeRnBP, EXACT, SPLIT><<<grid, kBlock, shm, s>>>(a); break;
-    case kModeRBP: k_eval_generic<KP, kModeRBP, EXACT, SPLIT><<<grid, kBlock, shm, s>>>(a); break;
-    default: k_eval_generic<KP, kModeEvalOnly, EXACT, SPLIT><<<grid, kBlock, shm, s>>>(a); break;
+    case kModeLBP: k_eval_generic<KP, kModeLBP><<<grid, kBlock, shm, s>>>(a); break;
+    case kModeRnBP: k_eval_generic<KP, kModeRnBP><<<grid, kBlock, shm, s>>>(a); break;
+    case kModeRBP: k_eval_generic<KP, kModeRBP><<<grid, kBlock, shm, s>>>(a); break;
+    default: k_eval_generic<KP, kModeEvalOnly><<<grid, kBlock, shm, s>>>(a); break;
     }
     return hipGetLastError();
 }
 
 template <int KP>
-static hipError_t launch_generic_k(int mode, const EvalArgs& a, int grid, size_t shm,
-                                   hipStream_t s) {
-    if (a.num_states != KP) return launch_generic_kp<KP, false>(mode, a, grid, shm, s);
-    if constexpr (KP * kBlock > kTileFloatsGeneric) {
-        // every tile on the lane-group path
-        if ((a.pair_kind == kPairShared || a.pair_kind == kPairSharedAsym) && !a.tile_big)
-            return launch_generic_kp<KP, true, true>(mode, a, grid, shm, s);
+static hipError_t launch_split(int mode, const EvalArgs& a, int grid, size_t shm, hipStream_t s) {
+    switch (mode) {
+    case kModeLBP: k_eval_split<KP, kModeLBP><<<grid, kBlock, shm, s>>>(a); break;
+    case kModeRnBP: k_eval_split<KP, kModeRnBP><<<grid, kBlock, shm, s>>>(a); break;
+    case kModeRBP: k_eval_split<KP, kModeRBP><<<grid, kBlock, shm, s>>>(a); break;
+    default: k_eval_split<KP, kModeEvalOnly><<<grid, kBlock, shm, s>>>(a); break;
     }
-    return launch_generic_kp<KP, true>(mode, a, grid, shm, s);
+    return hipGetLastError();
 }
 
-hipError_t launch_eval(int layout, int kp, int mode, const EvalArgs& a, hipStream_t s) {
+template <int TAB>
+static hipError_t launch_pairs(int mode, const EvalArgs& a, int grid, size_t shm, hipStream_t s) {
+    switch (mode) {
+    case kModeLBP: k_eval_pairs<kModeLBP, TAB><<<grid, kBlock, shm, s>>>(a); break;
+    case kModeRnBP: k_eval_pairs<kModeRnBP, TAB><<<grid, kBlock, shm, s>>>(a); break;
+    case kModeRBP: k_eval_pairs<kModeRBP, TAB><<<grid, kBlock, shm, s>>>(a); break;
+    default: k_eval_pairs<kModeEvalOnly, TAB><<<grid, kBlock, shm, s>>>(a); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_eval(int layout, int mode, const EvalArgs& a, hipStream_t s) {
     const int grid = 8 * a.tiles_per_xcd;
     if (grid <= 0) return hipSuccess;
     if (layout == kLayoutLogOdds) {
@@ -3102,12 +3674,9 @@ hipError_t launch_eval(int layout, int kp, int mode, const EvalArgs& a, hipStrea
         return hipGetLastError();
     }
     const int K = a.num_states;
-    const int TS = kTileFloatsGeneric / K;
     const int TN = a.tile_nodes_max;
     if (K == 32 && a.pair_kind == kPairShared && !a.tile_big && !a.no_mfma) {
-        // no shared table in LDS
-        const size_t shm = sizeof(float) * (size_t)(TS * (K + 1) + ((TN * (K + 1) + 3) & ~3)) +
-                           sizeof(int) * (size_t)(TS + TN + 1) + sizeof(unsigned short) * (size_t)TS;
+        const size_t shm = mfma32_lds_bytes(TN);
         if (a.mfma_bf16) {
             switch (mode) {
             case kModeLBP: k_eval_mfma32<kModeLBP, true><<<grid, kBlock, shm, s>>>(a); break;
@@ -3125,17 +3694,38 @@ hipError_t launch_eval(int layout, int kp, int mode, const EvalArgs& a, hipStrea
         }
         return hipGetLastError();
     }
-    const int tables = a.pair_kind == kPairSharedAsym ? 2 : 1;
+    if (a.pairs_route) {
+        const size_t shm =
+            pairs_lds_bytes(K, a.tile_slots_max, TN, a.pair_kind == kPairDense ? 0 : 1);
+        if (a.pair_kind == kPairDense) return launch_pairs<kTabDense>(mode, a, grid, shm, s);
+        // 32-wide matrix tiles for the symmetric tables
+        if (a.pair_kind == kPairShared && !a.no_mfma)
+            return launch_pairs<kTabMfma>(mode, a, grid, shm, s);
+        return launch_pairs<kTabShared>(mode, a, grid, shm, s);
+    }
+    const int TS = kTileFloatsGeneric / K;
+    const int tables = K <= 16 ? 0 : a.pair_kind == kPairSharedAsym ? 2 : 1;
     const size_t shm =
         sizeof(float) * (size_t)(TS * (K + 1) + ((TN * (K + 1) + 3) & ~3) + tables * K * K) +
         sizeof(int) * (size_t)(TS + TN + 1) + sizeof(unsigned short) * (size_t)TS;
-    switch (kp) {
-    case 2: return launch_generic_k<2>(mode, a, grid, shm, s);
-    case 4: return launch_generic_k<4>(mode, a, grid, shm, s);
-    case 8: return launch_generic_k<8>(mode, a, grid, shm, s);
-    case 16: return launch_generic_k<16>(mode, a, grid, shm, s);
-    case 32: return launch_generic_k<32>(mode, a, grid, shm, s);
-    case 64: return launch_generic_k<64>(mode, a, grid, shm, s);
+    switch (K) {
+    case 2: return launch_generic<2>(mode, a, grid, shm, s);
+    case 3: return launch_generic<3>(mode, a, grid, shm, s);
+    case 4: return launch_generic<4>(mode, a, grid, shm, s);
+    case 5: return launch_generic<5>(mode, a, grid, shm, s);
+    case 6: return launch_generic<6>(mode, a, grid, shm, s);
+    case 7: return launch_generic<7>(mode, a, grid, shm, s);
+    case 8: return launch_generic<8>(mode, a, grid, shm, s);
+    case 9: return launch_generic<9>(mode, a, grid, shm, s);
+    case 10: return launch_generic<10>(mode, a, grid, shm, s);
+    case 11: return launch_generic<11>(mode, a, grid, shm, s);
+    case 12: return launch_generic<12>(mode, a, grid, shm, s);
+    case 13: return launch_generic<13>(mode, a, grid, shm, s);
+    case 14: return launch_generic<14>(mode, a, grid, shm, s);
+    case 15: return launch_generic<15>(mode, a, grid, shm, s);
+    case 16: return launch_generic<16>(mode, a, grid, shm, s);
+    case 32: return launch_split<32>(mode, a, grid, shm, s);
+    case 64: return launch_split<64>(mode, a, grid, shm, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -3219,10 +3809,9 @@ hipError_t launch_close_run(const EvalArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_marginals(int layout, int kp, const int* node_ptr, const int* rev,
+hipError_t launch_marginals(int layout, const int* node_ptr, const int* rev,
                             const float* unary, const float* m, float* out, int N, int K,
                             hipStream_t s) {
-    (void)kp;
     if (N <= 0) return hipSuccess;
     const int grid = (N + 255) / 256;
     if (layout == kLayoutLogOdds)
