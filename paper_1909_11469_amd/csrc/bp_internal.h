@@ -88,6 +88,14 @@ struct alignas(128) CounterLine {
 };
 static_assert(sizeof(CounterLine) == 128, "one counter copy per cache line");
 
+// The top-k's radix select after some passes: the key bits fixed so far, how many
+// more keys to take among the keys with that prefix, and (after the last pass)
+// whether the keys equal to it are more than that, so that ties must be ranked.
+struct SelPick {
+    unsigned int prefix, mask, krem, rank;
+};
+constexpr int kHistCopies = 8;
+
 // Per-run scalar state on the device.
 struct DevState {
     unsigned int in_sel[4];         // which of the two buffers held m^t (by t & 3)
@@ -103,14 +111,10 @@ struct DevState {
     unsigned long long committed;   // committed messages in this run
     unsigned long long iterations;  // commits in this run
     unsigned long long evals;       // evaluations closed in this run
-    // greedy top-k selection (frontier residual BP)
-    unsigned int hist[16][256];     // copies of the digit histogram of a radix pass
-    unsigned int sel_prefix;        // key bits fixed so far
-    unsigned int sel_mask;
-    unsigned int sel_krem;          // how many more keys to take among the prefix
-    unsigned int sel_ties;          // keys equal to the final threshold
-    unsigned int sel_rank_ties;     // 1 if ties must be ranked by slot
-    unsigned int pad2[3];
+    // greedy top-k selection (frontier residual BP): copies of the digit histogram
+    // of each radix pass, and what the passes up to it have fixed
+    unsigned int hist[4][kHistCopies][256];
+    SelPick sel[4];
     // sparse re-evaluation: n_t by t & 3
     unsigned long long sp_n[4];
     // residual splash: length of the variable list of each level

@@ -686,7 +686,7 @@ __global__ __launch_bounds__(kBlockLO) void k_eval_logodds(EvalArgs a) {
     if (hist) {
         // the block's digit counts into one of the copies of the global histogram
         lds_barrier();
-        unsigned int* gh = &a.st->hist[blockIdx.x & 15][0];
+        unsigned int* gh = a.st->hist[0][blockIdx.x & (kHistCopies - 1)];
         for (int i = threadIdx.x; i < 256; i += kBlockLO)
             if (l.hist[i]) atomicAdd(&gh[i], l.hist[i]);
     }
@@ -2943,7 +2943,7 @@ __global__ void k_rbp_gate(DevState* st, const CounterLine* ctr, int slot) {
 // count and the commit: loaded as four 16-byte vectors, so that a thread's
 // loads are all in flight at once.
 constexpr int kSelPer = 16;
-constexpr int kHistCopies = 16;  // copies of the global digit histogram
+constexpr int kHistGrid = 1024;  // most blocks of a histogram pass
 static_assert(kCommitChunk == kSelBlock * kSelPer, "one commit chunk per block");
 
 // The keys (or slot indices) base[q0 .. q0+15], clamped to n (entries past n
@@ -2968,16 +2968,89 @@ __device__ __forceinline__ void sel_load16(const T* base, long long q0, long lon
     }
 }
 
+// What the passes of the select have fixed after the digit of pass `pass`, as
+// every block of the next launch works it out for itself from the histogram of
+// that pass (a launch of one block between two passes took 3.3 us, most of it
+// launch latency; 256 sums of kHistCopies words are in flight together here).
+// Digit b is the largest whose suffix count S(b) (keys with digit >= b) reaches the
+// number still to take, 0 if none.  Called by all kSelBlock threads; block 0
+// records the result for the launches after the next.
+struct SelShared {
+    unsigned int tot[kSelBlock / 64];
+    SelPick pick;
+};
+__device__ __forceinline__ SelPick sel_pick(DevState* st, int pass, unsigned int k, SelShared& s) {
+    const int b = threadIdx.x, lane = b & 63, w = b >> 6;
+    unsigned int hb = 0;
+#pragma unroll
+    for (int c = 0; c < kHistCopies; ++c) hb += st->hist[pass][c][b];
+    SelPick p{0u, 0u, k, 0u};
+    if (pass) p = st->sel[pass - 1];
+    // suffix sums: within the wave by shuffles, then the totals of the waves above
+    unsigned int S = hb;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned int y = (unsigned int)__shfl_down((int)S, o, 64);
+        if (lane + o < 64) S += y;
+    }
+    if (lane == 0) s.tot[w] = S;
+    __syncthreads();
+    for (int i = w + 1; i < kSelBlock / 64; ++i) S += s.tot[i];
+    const unsigned int S1 = S - hb;
+    if (b == 0 ? S1 < p.krem : (S >= p.krem && S1 < p.krem)) {
+        const int shift = 24 - 8 * pass;
+        p.prefix |= (unsigned int)b << shift;
+        p.mask |= 0xFFu << shift;
+        p.krem -= S1;
+        p.rank = pass == 3 && hb != p.krem ? 1u : 0u;
+        s.pick = p;
+        if (blockIdx.x == 0) st->sel[pass] = p;
+    }
+    __syncthreads();
+    return s.pick;
+}
+
+// Clear the histogram of a pass that no block of this launch reads or adds to.
+__device__ __forceinline__ void sel_clear(DevState* st, int pass) {
+    unsigned int* h = &st->hist[pass][0][0];
+    for (int i = blockIdx.x * kSelBlock + threadIdx.x; i < kHistCopies * 256; i += gridDim.x * kSelBlock)
+        h[i] = 0u;
+}
+
 // Digit histogram of pass `pass` (8 bits from the top) of the keys matching
-// the prefix fixed so far, over the chunks of kCommitChunk keys this block
-// takes (grid-stride), added into one of kHistCopies copies of the global
-// histogram (by block index) so that blocks do not queue on one address.
-__device__ __forceinline__ void rbp_hist_block(const DevState* st, const unsigned int* keys, int E,
-                                               int pass, unsigned int* ghist, unsigned int* h) {
+// the prefix fixed by the passes before (picked here, see sel_pick), over the
+// chunks of kCommitChunk keys this block takes (grid-stride), added into one of
+// kHistCopies copies (by block index) so that blocks do not queue on one address.
+// With gate_ctr (the first launch after an evaluation that counted digit 0) it is
+// also IsConverged for the top-k: nothing is selected or committed when that
+// evaluation found no residual above eps.  The histogram of pass p is read in
+// the launch after it, and cleared in the one after that (pass 3's in the next
+// iteration's pass 1).
+__global__ __launch_bounds__(kSelBlock) void k_rbp_hist(DevState* st, const unsigned int* keys,
+                                                        int E, int pass, unsigned int k,
+                                                        const CounterLine* gate_ctr) {
+    __shared__ unsigned int h[256];
+    __shared__ SelShared ss;
+    __shared__ unsigned int s_skip;
+    if (gate_ctr) {
+        if (threadIdx.x < 64) {
+            const unsigned int n = wave_sum32((unsigned int)gate_ctr[threadIdx.x].active);
+            if (threadIdx.x == 0) {
+                s_skip = (st->done || n == 0u) ? 1u : 0u;
+                if (blockIdx.x == 0) st->rbp_skip = s_skip;
+            }
+        }
+    } else if (threadIdx.x == 0) {
+        s_skip = st->rbp_skip;
+    }
     h[threadIdx.x] = 0u;
     __syncthreads();
-    const unsigned int prefix = pass ? st->sel_prefix : 0u;
-    const unsigned int mask = pass ? st->sel_mask : 0u;
+    if (s_skip) return;
+    SelPick p{0u, 0u, k, 0u};
+    if (pass) {
+        p = sel_pick(st, pass - 1, k, ss);
+        sel_clear(st, pass >= 2 ? pass - 2 : 3);
+    }
     const int shift = 24 - 8 * pass;
     const int chunks = (E + kCommitChunk - 1) / kCommitChunk;
     for (int c = blockIdx.x; c < chunks; c += gridDim.x) {
@@ -2986,82 +3059,11 @@ __device__ __forceinline__ void rbp_hist_block(const DevState* st, const unsigne
         sel_load16(keys, q0, (long long)E, v);
 #pragma unroll
         for (int j = 0; j < kSelPer; ++j)
-            lds_count(h, (v[j] >> shift) & 255u, q0 + j < E && (v[j] & mask) == prefix);
+            lds_count(h, (v[j] >> shift) & 255u, q0 + j < E && (v[j] & p.mask) == p.prefix);
     }
     __syncthreads();
     if (h[threadIdx.x])
-        atomicAdd(&ghist[(blockIdx.x & (kHistCopies - 1)) * 256 + threadIdx.x], h[threadIdx.x]);
-}
-
-// Pick the digit of pass `pass` (one block): the largest b whose suffix count
-// S(b) (keys with digit >= b) reaches the number still to take, digit 0 if
-// none; clear the histogram copies for the next pass.
-__device__ __forceinline__ void rbp_scan_block(DevState* st, int pass, unsigned int k,
-                                               unsigned int* ghist, unsigned int* h) {
-    const int b = threadIdx.x;
-    unsigned int hb = 0;
-#pragma unroll
-    for (int c = 0; c < kHistCopies; ++c) {
-        hb += ghist[c * 256 + b];
-        ghist[c * 256 + b] = 0u;
-    }
-    h[b] = hb;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        const unsigned int add = b + o < 256 ? h[b + o] : 0u;
-        __syncthreads();
-        h[b] += add;
-        __syncthreads();
-    }
-    const unsigned int krem = pass ? st->sel_krem : k;
-    const unsigned int S = h[b];
-    const unsigned int S1 = b < 255 ? h[b + 1] : 0u;
-    const bool pick = b == 0 ? S1 < krem : (S >= krem && S1 < krem);
-    if (pick) {
-        const unsigned int prefix = pass ? st->sel_prefix : 0u;
-        const unsigned int mask = pass ? st->sel_mask : 0u;
-        const int shift = 24 - 8 * pass;
-        const unsigned int left = krem - S1;
-        st->sel_prefix = prefix | ((unsigned int)b << shift);
-        st->sel_mask = mask | (0xFFu << shift);
-        st->sel_krem = left;
-        if (pass == 3) {
-            st->sel_ties = hb;
-            st->sel_rank_ties = (hb != left) ? 1u : 0u;
-        }
-    }
-}
-
-// One histogram pass (a block per chunk of kCommitChunk keys).
-__global__ __launch_bounds__(kSelBlock) void k_rbp_hist(DevState* st, const unsigned int* keys,
-                                                        int E, int pass) {
-    __shared__ unsigned int h[256];
-    if (st->rbp_skip) return;
-    rbp_hist_block(st, keys, E, pass, &st->hist[0][0], h);
-}
-
-// The digit pick of pass `pass`.  With gate_ctr (first pass only) it is also
-// IsConverged for the top-k: nothing is selected or committed when the
-// evaluation found no residual above eps (the copies that evaluation filled
-// are then left for the next run's reset).
-__global__ __launch_bounds__(kSelBlock) void k_rbp_scan(DevState* st, int pass, unsigned int k,
-                                                        const CounterLine* gate_ctr) {
-    __shared__ unsigned int h[256];
-    __shared__ unsigned int s_skip;
-    if (gate_ctr) {
-        if (threadIdx.x < 64) {
-            const unsigned int n = wave_sum32((unsigned int)gate_ctr[threadIdx.x].active);
-            if (threadIdx.x == 0) {
-                s_skip = (st->done || n == 0u) ? 1u : 0u;
-                st->rbp_skip = s_skip;
-            }
-        }
-    } else if (threadIdx.x == 0) {
-        s_skip = st->rbp_skip;
-    }
-    __syncthreads();
-    if (s_skip) return;
-    rbp_scan_block(st, pass, k, &st->hist[0][0], h);
+        atomicAdd(&st->hist[pass][blockIdx.x & (kHistCopies - 1)][threadIdx.x], h[threadIdx.x]);
 }
 
 // Ties at the threshold key are taken in (target, source) order.  Slots are
@@ -3069,13 +3071,19 @@ __global__ __launch_bounds__(kSelBlock) void k_rbp_scan(DevState* st, int pass, 
 // whose (target, source) is the (source, target) of slot p: walking positions
 // in order walks tied messages in (target, source) order.  Without rev the
 // positions are the keys' indices (residual splash ranks tied variables by id).
-// Each block counts the ties among its kCommitChunk positions.
+// The last digit is picked here (block 0 records it); when the threshold key has more
+// ties than are still to take, each block counts the ties among its kCommitChunk
+// positions.
 __global__ __launch_bounds__(kSelBlock) void k_rbp_tiecount(DevState* st, const unsigned int* keys,
                                                             const int* rev, int E,
                                                             unsigned int* block_ties) {
     __shared__ unsigned int part[kSelBlock / 64];
-    if (st->rbp_skip || !st->sel_rank_ties) return;
-    const unsigned int T = st->sel_prefix;
+    __shared__ SelShared ss;
+    if (st->rbp_skip) return;
+    const SelPick pk = sel_pick(st, 3, 0u, ss);
+    sel_clear(st, 2);
+    if (!pk.rank) return;
+    const unsigned int T = pk.prefix;
     const long long q0 = (long long)blockIdx.x * kCommitChunk + (long long)threadIdx.x * kSelPer;
     unsigned int c = 0;
     if (rev) {
@@ -3104,11 +3112,15 @@ __global__ __launch_bounds__(kSelBlock) void k_rbp_tiecount(DevState* st, const 
 }
 
 // Exclusive prefix sums of the nb block tie counts, in place (one block: each
-// thread takes a contiguous run, the run totals are scanned in LDS).
+// thread takes a contiguous run, the run totals are scanned in LDS).  Only for more
+// than kTieScanBlocks blocks: up to there a committing block adds up the counts
+// before its own itself, one load per thread and 256 blocks (a launch saved,
+// 1.4 us of it latency).
+constexpr int kTieScanBlocks = 2048;
 __global__ __launch_bounds__(kSelBlock) void k_rbp_tiescan(DevState* st, unsigned int* block_ties,
                                                            int nb) {
     __shared__ unsigned int part[kSelBlock];
-    if (st->rbp_skip || !st->sel_rank_ties) return;
+    if (st->rbp_skip || !st->sel[3].rank) return;
     const int per = (nb + kSelBlock - 1) / kSelBlock;
     const int r0 = threadIdx.x * per, r1 = min(nb, r0 + per);
     unsigned int run = 0;
@@ -3129,6 +3141,20 @@ __global__ __launch_bounds__(kSelBlock) void k_rbp_tiescan(DevState* st, unsigne
     }
 }
 
+// Ties before block blockIdx.x (called by all kSelBlock threads).
+__device__ __forceinline__ unsigned int ties_before(const unsigned int* block_ties, bool scanned,
+                                                    unsigned int* s_w) {
+    if (scanned) return block_ties[blockIdx.x];
+    unsigned int c = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kSelBlock) c += block_ties[i];
+    c = wave_sum32(c);
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = c;
+    __syncthreads();
+    c = 0;
+    for (int i = 0; i < kSelBlock / 64; ++i) c += s_w[i];
+    return c;
+}
+
 // Commit the frontier: every key above the threshold, and among keys equal to
 // it the first sel_krem in position order (ranked ties) or all of them.  A
 // thread takes kSelPer consecutive positions; the ties before it come from an
@@ -3137,13 +3163,14 @@ __global__ __launch_bounds__(kSelBlock) void k_rbp_commit(DevState* st, unsigned
                                                           const int* rev, const float* cand,
                                                           float* m, int E, int row, int all,
                                                           const unsigned int* block_ties,
-                                                          RbpSparse sp, const int* moff) {
+                                                          RbpSparse sp, const int* moff,
+                                                          int scanned) {
     __shared__ unsigned int part[kSelBlock / 64];
     __shared__ unsigned int s_cm[kSelBlock / 64];
     if (st->rbp_skip) return;
-    const unsigned int T = st->sel_prefix;
-    const bool rank = !all && st->sel_rank_ties;
-    const unsigned int krem = st->sel_krem;
+    const unsigned int T = st->sel[3].prefix;
+    const bool rank = !all && st->sel[3].rank;
+    const unsigned int krem = st->sel[3].krem;
     const long long q0 = (long long)blockIdx.x * kCommitChunk + (long long)threadIdx.x * kSelPer;
     int e[kSelPer];
     if (rank) {
@@ -3187,7 +3214,7 @@ __global__ __launch_bounds__(kSelBlock) void k_rbp_commit(DevState* st, unsigned
         }
         if (lane == 63) part[w] = x;
         __syncthreads();
-        unsigned int before = block_ties[blockIdx.x] + x - c;
+        unsigned int before = ties_before(block_ties, scanned, s_cm) + x - c;
         for (int i = 0; i < w; ++i) before += part[i];
 #pragma unroll
         for (int j = 0; j < kSelPer; ++j) {
@@ -3195,6 +3222,7 @@ __global__ __launch_bounds__(kSelBlock) void k_rbp_commit(DevState* st, unsigned
             if (before < krem) take |= 1u << j;
             ++before;
         }
+        __syncthreads();  // s_cm is reused below
     }
     unsigned int cm = 0;  // committed messages whose residual was above eps
     if (take && row == 1) {
@@ -3380,16 +3408,18 @@ __global__ __launch_bounds__(kBlock) void k_rs_vkeys(RsArgs r) {
 // `all`); each is marked in level 0 and appended to list 0.  Same chunking as
 // the tie count (kSelPer consecutive variables per thread).
 __global__ __launch_bounds__(kSelBlock) void k_rs_roots(RsArgs r, int all,
-                                                        const unsigned int* block_ties) {
+                                                        const unsigned int* block_ties,
+                                                        int scanned) {
     __shared__ unsigned int part[kSelBlock / 64];
+    __shared__ unsigned int s_tb[kSelBlock / 64];
     __shared__ unsigned int s_w[kBlock / 64 + 1];
     static_assert(kSelBlock == kBlock, "block_append assumes kBlock threads");
     const DevState* st = r.st;
     if (st->rbp_skip) return;
     const int N = r.num_nodes;
-    const unsigned int T = st->sel_prefix;
-    const bool rank = !all && st->sel_rank_ties;
-    const unsigned int krem = st->sel_krem;
+    const unsigned int T = st->sel[3].prefix;
+    const bool rank = !all && st->sel[3].rank;
+    const unsigned int krem = st->sel[3].krem;
     const long long q0 = (long long)blockIdx.x * kCommitChunk + (long long)threadIdx.x * kSelPer;
     unsigned int take = 0, tie = 0;
     if (all) {
@@ -3418,7 +3448,7 @@ __global__ __launch_bounds__(kSelBlock) void k_rs_roots(RsArgs r, int all,
         }
         if (lane == 63) part[w] = x;
         __syncthreads();
-        unsigned int before = block_ties[blockIdx.x] + x - c;
+        unsigned int before = ties_before(block_ties, scanned, s_tb) + x - c;
         for (int i = 0; i < w; ++i) before += part[i];
 #pragma unroll
         for (int j = 0; j < kSelPer; ++j) {
@@ -3911,12 +3941,15 @@ hipError_t launch_rbp_select(DevState* st, const unsigned int* keys, const int* 
                              unsigned int* block_ties, hipStream_t s) {
     const int nb = (E + kCommitChunk - 1) / kCommitChunk;
     const int grid = nb > 0 ? nb : 1;
-    for (int pass = 0; pass < 4; ++pass) {
-        if (pass > 0 || !hist0_done) k_rbp_hist<<<grid, kSelBlock, 0, s>>>(st, keys, E, pass);
-        k_rbp_scan<<<1, kSelBlock, 0, s>>>(st, pass, k, pass == 0 ? gate_ctr : nullptr);
+    // few enough blocks that their adds to one histogram word stay short
+    const int hgrid = std::min(grid, kHistGrid);
+    const CounterLine* gate = gate_ctr;  // the first launch
+    for (int pass = hist0_done ? 1 : 0; pass < 4; ++pass) {
+        k_rbp_hist<<<hgrid, kSelBlock, 0, s>>>(st, keys, E, pass, k, gate);
+        gate = nullptr;
     }
     k_rbp_tiecount<<<grid, kSelBlock, 0, s>>>(st, keys, rev, E, block_ties);
-    k_rbp_tiescan<<<1, kSelBlock, 0, s>>>(st, block_ties, nb);
+    if (nb > kTieScanBlocks) k_rbp_tiescan<<<1, kSelBlock, 0, s>>>(st, block_ties, nb);
     return hipGetLastError();
 }
 
@@ -3928,7 +3961,7 @@ hipError_t launch_rbp_commit(DevState* st, unsigned int* keys, const int* rev,
     const int nb = (E + kCommitChunk - 1) / kCommitChunk;
     if (nb <= 0) return hipSuccess;
     k_rbp_commit<<<nb, kSelBlock, 0, s>>>(st, keys, rev, cand, m, E, row, all, block_ties, sp,
-                                         moff);
+                                         moff, nb > kTieScanBlocks ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -3958,7 +3991,8 @@ hipError_t launch_rs_select(const RsArgs& r, unsigned int k, int all, unsigned i
         hipError_t e = launch_rbp_select(r.st, r.vkey, nullptr, N, k, nullptr, 0, block_ties, s);
         if (e != hipSuccess) return e;
     }
-    k_rs_roots<<<(N + kCommitChunk - 1) / kCommitChunk, kSelBlock, 0, s>>>(r, all, block_ties);
+    const int nb = (N + kCommitChunk - 1) / kCommitChunk;
+    k_rs_roots<<<nb, kSelBlock, 0, s>>>(r, all, block_ties, nb > kTieScanBlocks ? 1 : 0);
     if (r.depth >= 1) {
         k_rs_bfs<<<rs_grid(N), kBlock, 0, s>>>(r);
         k_rs_lists<<<kRsListGrid, kBlock, 0, s>>>(r);
@@ -3993,7 +4027,7 @@ hipError_t launch_fill_u32(unsigned int* p, unsigned int v, long long n, hipStre
 #include <mutex>
 
 namespace {
-constexpr size_t kNoAllocScratchBytes = size_t(1) << 20;  // graphs up to ~10^9 messages
+constexpr size_t kNoAllocScratchBytes = (size_t(1) << 20) + (size_t(1) << 15);  // graphs up to ~10^9 messages
 constexpr int kNoAllocMaxDevices = 64;
 std::mutex g_noalloc_mu;
 char* g_noalloc_ptr[kNoAllocMaxDevices];
