@@ -486,11 +486,11 @@ __device__ __forceinline__ void tile_load_const(TileRegs& d, const EvalArgs& a, 
         d.ptr[j] = ld32(a.node_ptr, d.n0 + min(v, d.nn));
         d.u[j] = ld32(a.unary, d.n0 + min(v, max(d.nn - 1, 0)));
     }
-    // a tile without slots reads slot s0, which lies inside the graph's
-    // device arena (the arrays are carved from one allocation in sequence)
+    // a tile without slots reads slot 0 (its own s0 may be one past the last
+    // slot, and what lies there is no slot to gather from)
 #pragma unroll
     for (int k = 0; k < kPP; ++k) {
-        const int s = d.s0 + min(tid + k * kBlockLO, max(d.ns - 1, 0));
+        const int s = d.ns > 0 ? d.s0 + min(tid + k * kBlockLO, d.ns - 1) : 0;
         d.rev[k] = R16 ? s + (int)ld16(a.rev16, s) : ld32(a.rev, s);
         d.J[k] = ld32(a.coupling, s);
     }
@@ -499,7 +499,7 @@ __device__ __forceinline__ void tile_load_const(TileRegs& d, const EvalArgs& a, 
 __device__ __forceinline__ void tile_load_msgs(TileRegs& d, const float* m_in) {
 #pragma unroll
     for (int k = 0; k < kPP; ++k)
-        d.old[k] = ld32(m_in, d.s0 + min((int)threadIdx.x + k * kBlockLO, max(d.ns - 1, 0)));
+        d.old[k] = ld32(m_in, d.ns > 0 ? d.s0 + min((int)threadIdx.x + k * kBlockLO, d.ns - 1) : 0);
 }
 
 template <int MODE, bool R16 = false>
