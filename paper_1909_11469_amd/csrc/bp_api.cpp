@@ -506,6 +506,7 @@ struct bp_graph {
     long long t_next = 0;        // global iteration number of the next evaluation
     long long prev_active = -1;  // n_{t_next - 1}
     DevState* host_state = nullptr;  // pinned mirror
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;  // timing of a run (run_events)
     int num_cus = 0;                 // compute units of the device
     int resident[4] = {0, 0, 0, 0};  // log-odds eval blocks resident per CU, by mode
     int lo_grid = 0;                 // tuned persistent grid of the K = 2 kernel (0: not yet)
@@ -670,6 +671,8 @@ void bp_destroy_graph(bp_graph* g) {
         if (g->sparse_owned && g->sparse_mem) (void)hipFree(g->sparse_mem);
         if (g->splash_owned && g->splash_mem) (void)hipFree(g->splash_mem);
         if (g->host_state) (void)hipHostFree(g->host_state);
+        if (g->ev0) (void)hipEventDestroy(g->ev0);
+        if (g->ev1) (void)hipEventDestroy(g->ev1);
     }
     delete g;
 }
@@ -812,6 +815,61 @@ struct RunScratch {
     bool noalloc;  // no events, no buffer allocation
 };
 
+// The two timing events of a graph's runs, created by its first run.
+static hipError_t run_events(bp_graph* g) {
+    hipError_t e = hipSuccess;
+    if (!g->ev0) e = hipEventCreate(&g->ev0);
+    if (e == hipSuccess && !g->ev1) e = hipEventCreate(&g->ev1);
+    return e;
+}
+
+// A run of a small K = 2 graph (k_solve_small): launches of at most
+// kSmallCommits commits each, until it converged or the bound is reached.
+static int run_small(bp_graph* g, int mode, EvalArgs a, const bp_run_opts& o, bp_run_stats* stats,
+                     bool timed) {
+    hipStream_t s = g->stream;
+    SmallState* out = reinterpret_cast<SmallState*>(g->host_state);
+    if (timed) {
+        HIP_OK(run_events(g), "event");
+        HIP_OK(hipEventRecord(g->ev0, s), "event record");
+    }
+    long long commits = 0;
+    unsigned long long committed = 0;
+    a.it = 0;
+    a.t = (unsigned int)g->t_next;
+    a.prev_active_host = g->prev_active;
+    for (bool fresh = !o.warm_start;; fresh = false) {
+        HIP_OK(launch_solve_small(mode, a, g->cur(), fresh ? 1 : 0,
+                                  std::min<long long>(kSmallCommits, o.max_iters - commits), out, s),
+               "small solve");
+        if (timed) HIP_OK(hipEventRecord(g->ev1, s), "event record");
+        HIP_OK(hipStreamSynchronize(s), "synchronize");
+        commits += out->commits;
+        committed += out->committed;
+        a.t = (unsigned int)out->t;
+        a.prev_active_host = out->prev;
+        if (out->done || commits >= o.max_iters) break;
+    }
+    float ms = 0.0f;
+    if (timed) HIP_OK(hipEventElapsedTime(&ms, g->ev0, g->ev1), "event time");
+    g->t_next = out->t;
+    g->prev_active = out->prev;
+    if (stats) {
+        std::memset(stats, 0, sizeof(*stats));
+        stats->iterations = commits;
+        stats->converged = out->done ? 1 : 0;
+        stats->last_active = out->n;
+        float rm;
+        std::memcpy(&rm, &out->rmax, sizeof(rm));
+        stats->last_max_residual = rm;
+        stats->evaluated = (commits + 1) * g->L.E;
+        stats->committed = (long long)committed;
+        stats->final_t = out->t;
+        stats->device_ms = ms;
+    }
+    return out->done ? BP_OK : BP_NOT_CONVERGED;
+}
+
 static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t seed,
                     const bp_run_opts* opts, bp_run_stats* stats, const RunScratch& rs) {
     if (!g) return fail(BP_EINVAL, "graph is NULL");
@@ -915,9 +973,18 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
         g->splash_owned = owned;
         g->rs_tag = 0;
     }
+    // Small K = 2 graphs: the whole run in one block (k_solve_small).  An iteration of
+    // a 20 x 20 grid takes 1.2 us there and 5.3 us as a launch; at 3,842 messages
+    // 2.2 us (LBP) and 3.1 us (RnBP), 7.0 us against 32 with the top-k.  One compute
+    // unit's time doubles with the messages, so past 4,096 launches over the whole
+    // device catch up.
+    const bool small = L.layout == kLayoutLogOdds && L.big4.empty() && L.E <= kSmallMax &&
+                       L.N <= kSmallMax && !o.sparse && !splash && !o.profile;
     if (!o.warm_start) {
         const float uni = L.layout == kLayoutLogOdds ? 0.0f : 1.0f / (float)L.K;
-        if (L.layout == kLayoutRagged)
+        if (small) {
+            // the kernel starts from uniform messages itself
+        } else if (L.layout == kLayoutRagged)
             HIP_OK(launch_fill_ragged(g->cur(), g->at<int>(g->off.moff), (int)L.E, s), "fill");
         else
             HIP_OK(launch_fill(g->cur(), uni, L.msg_floats, s), "fill");
@@ -926,8 +993,6 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
     }
     if (g->t_next + o.max_iters + 1 > 0xFFFFFFFFLL)
         return fail(BP_EINVAL, "iteration counter would pass 2^32");
-    HIP_OK(launch_init_state(rs.st, rs.ctr, s), "init state");
-
     // residual splash evaluates with the frontier-RBP kernels (in place)
     const int mode = schedule == BP_LBP ? kModeLBP
                      : (schedule == BP_RBP || splash) ? kModeRBP
@@ -936,6 +1001,8 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
     EvalArgs a = run_args(g, schedule, eps, p, seed, o, rbp_k);
     a.st = rs.st;
     a.ctr = rs.ctr;
+    if (small) return run_small(g, mode, a, o, stats, !rs.noalloc);
+    HIP_OK(launch_init_state(rs.st, rs.ctr, s), "init state");
     // frontier RBP on the K = 2 kernel: the evaluation also counts the top-k's
     // first radix digit (not for oversized nodes, the sparse phase, or k = E)
     a.hist0 = (mode == kModeRBP && !splash && L.layout == kLayoutLogOdds && a.num_big == 0 &&
@@ -978,8 +1045,9 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
     }
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (!rs.noalloc) {
-        HIP_OK(hipEventCreate(&ev0), "event");
-        HIP_OK(hipEventCreate(&ev1), "event");
+        HIP_OK(run_events(g), "event");
+        ev0 = g->ev0;
+        ev1 = g->ev1;
     }
     // profile = k > 0.  When the evaluation kernel is the only launch of an
     // iteration (LBP / RnBP without oversized nodes), a pair of events brackets
@@ -1210,11 +1278,7 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
            "state readback");
     HIP_OK(hipStreamSynchronize(s), "synchronize");
     float total_ms = 0.0f;
-    if (ev0) {
-        HIP_OK(hipEventElapsedTime(&total_ms, ev0, ev1), "event time");
-        (void)hipEventDestroy(ev0);
-        (void)hipEventDestroy(ev1);
-    }
+    if (ev0) HIP_OK(hipEventElapsedTime(&total_ms, ev0, ev1), "event time");
     for (auto& x : kev) (void)hipEventDestroy(x);
     for (auto& x : tev) (void)hipEventDestroy(x);
 

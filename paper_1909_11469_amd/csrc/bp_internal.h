@@ -191,6 +191,22 @@ struct EvalArgs {
     int sp_first;               // first sparse iteration of a run (stored residuals invalid)
 };
 
+// Small K = 2 graphs (at most kSmallMax messages and as many variables): a whole run
+// in one block, up to kSmallCommits commits per launch; the launch reports here
+// (pinned host memory).
+constexpr int kSmallPer = 4;
+constexpr int kSmallMax = 1024 * kSmallPer;
+constexpr long long kSmallCommits = 16384;
+struct SmallState {
+    unsigned int done;              // the last evaluation found n_t == 0
+    unsigned int rmax;              // R_t of the last evaluation
+    long long t;                    // its t
+    long long n;                    // its n_t
+    long long prev;                 // n_{t-1} (-1 if none)
+    long long commits;              // iterations of the launch that committed
+    unsigned long long committed;   // messages committed by them
+};
+
 // One graph of a serving batch (device memory).  `a` holds the graph's
 // arguments as bp_run would set them; before every batched launch a small
 // kernel sets the per-launch fields (t, it, in_buf, out_buf, the mode of the
@@ -229,6 +245,9 @@ hipError_t launch_init_state(DevState* st, CounterLine* ctr, hipStream_t s);
 hipError_t launch_fill(float* p, float v, long long n, hipStream_t s);
 hipError_t launch_eval(int layout, int mode, const EvalArgs& a, hipStream_t s);
 hipError_t launch_close_run(const EvalArgs& a, hipStream_t s);
+// fresh: start from uniform messages instead of msg.  mode: kModeLBP / RnBP / RBP.
+hipError_t launch_solve_small(int mode, const EvalArgs& a, float* msg, int fresh,
+                              long long max_commits, SmallState* out, hipStream_t s);
 int logodds_blocks_per_cu(int mode);
 hipError_t launch_marginals(int layout, const int* node_ptr, const int* rev,
                             const float* unary, const float* m, float* out, int N, int K,

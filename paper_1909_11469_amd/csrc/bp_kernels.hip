@@ -3330,6 +3330,267 @@ __global__ void k_sparse_rbp_close(EvalArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// Whole runs of small K = 2 graphs in one block: at most kSmallPer messages and
+// variables per thread, every array of the iteration in LDS or registers.
+//
+// A launch per iteration costs such a graph 5 us (32 us with the top-k's six
+// launches) whatever its size: the launch, the counters and the messages from
+// memory, each a latency of its own.  Here an iteration is three barriers
+// (a few more for the top-k), and n_t is known before the commit, so only the
+// outcome that p_t chooses is written.  The arithmetic per message is the tiled
+// kernel's, the incoming messages are summed in slot order as it sums them, the
+// draws are the same words: the results are bit for bit the same.
+//
+// LDS: in[s] holds the message into the source of slot s (that of slot rev[s]),
+// so a commit of slot s writes in[rev[s]].  A launch takes up to max_commits
+// commits (the run's bound, cut so that one launch stays short), closes with an
+// evaluation and leaves the messages in memory.
+// ---------------------------------------------------------------------------
+template <int NT>
+struct SmallLds {
+    float in[NT * kSmallPer];
+    float L[NT * kSmallPer];             // node aggregates
+    unsigned int u[NT * kSmallPer];      // 24-bit uniforms (RnBP)
+    unsigned short ptr[NT * kSmallPer + 1];
+    unsigned int hist[256];              // top-k
+    unsigned int ties[NT * kSmallPer / 32];
+    unsigned int pick[4];
+    unsigned int n[2][NT / 64], rm[2][NT / 64];
+    unsigned int tot[4];
+    unsigned long long cm[NT / 64];
+};
+
+// The rbp_k largest residual keys of the block's slots, ties by position (see
+// k_rbp_tiecount: slot e is at position rev[e]); bit k of the result: the
+// thread's slot tid + k NT is taken.
+template <int NT>
+__device__ __forceinline__ unsigned int small_topk(SmallLds<NT>& l, int E, unsigned int k,
+                                                   const float* r, const int* rev) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    unsigned int prefix = 0, mask = 0, krem = k, ties = 0;
+    for (int pass = 0; pass < 4; ++pass) {
+        const int shift = 24 - 8 * pass;
+        if (tid < 256) l.hist[tid] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kSmallPer; ++j) {
+            const unsigned int key = __float_as_uint(r[j]);
+            lds_count(l.hist, (key >> shift) & 255u, tid + j * NT < E && (key & mask) == prefix);
+        }
+        __syncthreads();
+        // the pick (as sel_pick), four digits per lane of one wave
+        if (tid < 64) {
+            unsigned int h[4], S = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                h[i] = l.hist[4 * lane + i];
+                S += h[i];
+            }
+            const unsigned int own = S;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned int y = (unsigned int)__shfl_down((int)S, o, 64);
+                if (lane + o < 64) S += y;
+            }
+            unsigned int above = S - own;  // keys with a digit of a higher lane
+#pragma unroll
+            for (int i = 3; i >= 0; --i) {
+                const unsigned int Sb = above + h[i];
+                if (4 * lane + i == 0 ? above < krem : (Sb >= krem && above < krem)) {
+                    l.pick[0] = (unsigned int)(4 * lane + i);
+                    l.pick[1] = krem - above;
+                    l.pick[2] = h[i];
+                }
+                above = Sb;
+            }
+        }
+        __syncthreads();
+        prefix |= l.pick[0] << shift;
+        mask |= 0xFFu << shift;
+        krem = l.pick[1];
+        ties = l.pick[2];
+    }
+    const bool rank = ties != krem;
+    if (rank) {
+        for (int i = tid; i < NT * kSmallPer / 32; i += NT) l.ties[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kSmallPer; ++j)
+            if (tid + j * NT < E && __float_as_uint(r[j]) == prefix)
+                atomicOr(&l.ties[rev[j] >> 5], 1u << (rev[j] & 31));
+        __syncthreads();
+    }
+    unsigned int take = 0;
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) {
+        if (tid + j * NT >= E) continue;
+        const unsigned int key = __float_as_uint(r[j]);
+        bool t = key > prefix;
+        if (key == prefix) {
+            t = true;
+            if (rank) {
+                unsigned int before = __popc(l.ties[rev[j] >> 5] & ((1u << (rev[j] & 31)) - 1u));
+                for (int i = 0; i < rev[j] >> 5; ++i) before += __popc(l.ties[i]);
+                t = before < krem;
+            }
+        }
+        take |= (t ? 1u : 0u) << j;
+    }
+    return take;
+}
+
+template <int MODE, int NT>
+__global__ __launch_bounds__(NT) void k_solve_small(EvalArgs a, float* msg, int fresh,
+                                                    long long max_commits, SmallState* out) {
+    __shared__ SmallLds<NT> l;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int E = (int)a.num_messages, N = a.num_nodes;
+    // the thread's slots tid + k NT and nodes tid + k NT
+    float J[kSmallPer], old[kSmallPer], u[kSmallPer];
+    int rev[kSmallPer], owner[kSmallPer];
+#pragma unroll
+    for (int k = 0; k < kSmallPer; ++k) {
+        const int s = tid + k * NT, v = tid + k * NT;
+        rev[k] = 0;
+        J[k] = old[k] = u[k] = 0.0f;
+        if (s < E) {
+            rev[k] = a.rev[s];
+            J[k] = a.coupling[s];
+            old[k] = fresh ? 0.0f : msg[s];
+            l.in[s] = fresh ? 0.0f : msg[rev[k]];
+        }
+        if (v < N) {
+            u[k] = a.unary[v];
+            const int p0 = a.node_ptr[v], p1 = a.node_ptr[v + 1];
+            l.ptr[v] = (unsigned short)p0;
+            if (v == N - 1) l.ptr[N] = (unsigned short)p1;
+            // l.u holds the owners until they are in registers
+            for (int q = p0; q < p1; ++q) l.u[q] = (unsigned int)v;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSmallPer; ++k) owner[k] = tid + k * NT < E ? (int)l.u[tid + k * NT] : 0;
+    __syncthreads();
+    long long n_prev = a.prev_active_host;
+    unsigned int t = a.t;
+    unsigned long long committed = 0;  // per thread
+    long long commits = 0;
+    unsigned int n_last, rm_last;
+    long long prev_last;
+    bool done = false;
+    for (;;) {
+        // node aggregates, incoming messages in slot order; RnBP: the draws
+#pragma unroll
+        for (int k = 0; k < kSmallPer; ++k) {
+            const int v = tid + k * NT;
+            if (v >= N) break;
+            const int q0 = l.ptr[v], q1 = l.ptr[v + 1];
+            float L = u[k];
+            for (int q = q0; q < q1; ++q) L += l.in[q];
+            l.L[v] = L;
+            if (MODE == kModeRnBP) {
+                for (int q = q0; q < q1; q += 4) {
+                    const uint4 x = philox4((unsigned int)v, (unsigned int)(q - q0) >> 2, t, a.key0,
+                                            a.key1);
+                    l.u[q] = x.x >> 8;
+                    if (q + 1 < q1) l.u[q + 1] = x.y >> 8;
+                    if (q + 2 < q1) l.u[q + 2] = x.z >> 8;
+                    if (q + 3 < q1) l.u[q + 3] = x.w >> 8;
+                }
+            }
+        }
+        __syncthreads();
+        float cand[kSmallPer], r[kSmallPer];
+        unsigned int act = 0, acts = 0;  // bit k: slot k active; their number
+        float rmax = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kSmallPer; ++k) {
+            const int s = tid + k * NT;
+            cand[k] = r[k] = 0.0f;
+            if (s < E) {
+                cand[k] = logodds_update(l.L[owner[k]], l.in[s], J[k]);
+                r[k] = fabsf(sigmoid_fast(cand[k]) - sigmoid_fast(old[k]));
+                rmax = fmaxf(rmax, r[k]);
+                if (r[k] > a.eps) {
+                    act |= 1u << k;
+                    ++acts;
+                }
+            }
+        }
+        // n_t and R_t (two sets in turn, so that one barrier separates them)
+        const int par = (int)(t & 1u);
+        const unsigned int wn = dpp_sum_last(acts), wr = dpp_max_last(__float_as_uint(rmax));
+        if (lane == 63) {
+            l.n[par][w] = wn;
+            l.rm[par][w] = wr;
+        }
+        __syncthreads();
+        unsigned int n = 0, rm = 0;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) {
+            n += l.n[par][i];
+            rm = max(rm, l.rm[par][i]);
+        }
+        n_last = n;
+        rm_last = rm;
+        prev_last = n_prev;
+        done = n == 0u;
+        if (done || commits == max_commits) break;
+        unsigned int take;  // bit k: slot k is committed
+        if (MODE == kModeLBP) {
+            take = ~0u;
+        } else if (MODE == kModeRnBP) {
+            const unsigned int thr =
+                select_outcome(a, (unsigned long long)n, n_prev) ? a.thr_b : a.thr_a;
+            take = 0u;
+#pragma unroll
+            for (int k = 0; k < kSmallPer; ++k)
+                if ((act >> k & 1u) && l.u[tid + k * NT] < thr) take |= 1u << k;
+            committed += __popc(take);
+        } else {
+            take = a.rbp_k >= (unsigned long long)E
+                       ? ~0u
+                       : small_topk<NT>(l, E, (unsigned int)a.rbp_k, r, rev);
+        }
+#pragma unroll
+        for (int k = 0; k < kSmallPer; ++k) {
+            if (tid + k * NT < E && (take >> k & 1u)) {
+                old[k] = cand[k];
+                l.in[rev[k]] = cand[k];
+            }
+        }
+        ++commits;
+        ++t;
+        n_prev = (long long)n;
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < kSmallPer; ++k)
+        if (tid + k * NT < E) msg[tid + k * NT] = old[k];
+    if (MODE == kModeRnBP) {
+        // at most kSmallPer commits per thread and iteration: below 2^32 per launch
+        const unsigned int c = dpp_sum_last((unsigned int)committed);
+        if (lane == 63) l.cm[w] = c;
+        __syncthreads();
+    }
+    if (tid == 0) {
+        unsigned long long cm = 0;
+        if (MODE == kModeRnBP)
+            for (int i = 0; i < NT / 64; ++i) cm += l.cm[i];
+        else
+            cm = (unsigned long long)commits * (MODE == kModeLBP ? (unsigned long long)E : a.rbp_k);
+        out->done = done ? 1u : 0u;
+        out->rmax = rm_last;
+        out->t = (long long)t;
+        out->n = (long long)n_last;
+        out->prev = prev_last;
+        out->commits = commits;
+        out->committed = cm;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Residual splash (Sec. II-B, Sec. III-A) in frontier form, K = 2 log-odds
 // layout, messages committed in place.  After the evaluation of iteration t
 // (the candidate and residual key of every message, as for frontier RBP):
@@ -3832,6 +4093,28 @@ hipError_t batch_graph_nodes(BatchGraph* graphs, int num_graphs, const int* list
     }
     *out = gr;
     return hipSuccess;
+}
+
+template <int NT>
+static hipError_t launch_small_nt(int mode, const EvalArgs& a, float* msg, int fresh,
+                                  long long max_commits, SmallState* out, hipStream_t s) {
+    switch (mode) {
+    case kModeLBP: k_solve_small<kModeLBP, NT><<<1, NT, 0, s>>>(a, msg, fresh, max_commits, out); break;
+    case kModeRnBP: k_solve_small<kModeRnBP, NT><<<1, NT, 0, s>>>(a, msg, fresh, max_commits, out); break;
+    default: k_solve_small<kModeRBP, NT><<<1, NT, 0, s>>>(a, msg, fresh, max_commits, out); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_solve_small(int mode, const EvalArgs& a, float* msg, int fresh,
+                              long long max_commits, SmallState* out, hipStream_t s) {
+    // the fewest waves that hold the graph: fewer to meet at each barrier
+    const long long most = std::max<long long>((long long)a.num_messages, a.num_nodes);
+    if (most <= 256 * kSmallPer)
+        return launch_small_nt<256>(mode, a, msg, fresh, max_commits, out, s);
+    if (most <= 512 * kSmallPer)
+        return launch_small_nt<512>(mode, a, msg, fresh, max_commits, out, s);
+    return launch_small_nt<1024>(mode, a, msg, fresh, max_commits, out, s);
 }
 
 hipError_t launch_close_run(const EvalArgs& a, hipStream_t s) {
