@@ -90,6 +90,9 @@ struct HostLayout {
     std::vector<int> moff;            // [E+1] message row of each slot (K_target entries)
     std::vector<int> toff;            // [E+1] table of each slot (K_source x K_target)
     std::vector<int> heavy;           // {slot, source} of the slots of heavy variables
+    std::vector<int> vrec;            // [][8] records of the other variables (EvalArgs::vrec)
+    int num_wide = 0;                 // the first records, which take a block each
+    std::vector<int> rin;             // [E] message row of the reverse slot
     std::vector<long long> coff;      // [E+1] row of each canonical message in host arrays
     long long msg_floats = 0;         // entries of one message buffer
     long long belief_floats = 0;      // entries of the beliefs (N K, or sum K_i)
@@ -106,7 +109,7 @@ struct Arena {
 
 struct Offsets {
     size_t node_ptr, rev, tile, tile_slot, tiles4, big4, coupling, unary, pair, orient, msg[4], cand, keys, ties, state,
-        ctr, marg, kv, uoff, moff, toff, heavy, rev16, sparse, splash, total;
+        ctr, marg, kv, uoff, moff, toff, heavy, vrec, rin, rev16, sparse, splash, total;
 };
 
 // Device bytes of the sparse re-evaluation buffers of a log-odds graph: dirty
@@ -143,6 +146,8 @@ Offsets plan(const HostLayout& L) {
     o.moff = a.take(sizeof(int) * L.moff.size());
     o.toff = a.take(sizeof(int) * L.toff.size());
     o.heavy = a.take(sizeof(int) * L.heavy.size());
+    o.vrec = a.take(sizeof(int) * L.vrec.size());
+    o.rin = a.take(sizeof(int) * L.rin.size());
     o.rev16 = a.take(sizeof(short) * L.rev16.size());
     o.sparse = L.sparse_reserved ? a.take(sparse_bytes(L)) : 0;
     o.splash = L.splash_reserved ? a.take(splash_bytes(L.N)) : 0;
@@ -318,15 +323,35 @@ int build_layout(const bp_graph_desc* d, HostLayout& L) {
             L.toff[s + 1] = L.toff[s] + ki * kj;
         }
         L.msg_floats = L.moff[E];
-        // slots of heavy variables: each is evaluated by a wave of its own
+        L.rin.resize((size_t)E);
+        for (long long s = 0; s < E; ++s) L.rin[s] = L.moff[L.rev[s]];
+        // slots of heavy variables: each is evaluated by a wave of its own.  The
+        // other variables by falling power of two of their product work, so that
+        // the longest waves start first (in id order within one)
+        std::vector<int> by_work[32];
         for (long long i = 0; i < N; ++i) {
             const int s0 = L.node_ptr[i], s1 = L.node_ptr[i + 1];
-            if (ragged_flat(s1 - s0, L.kv[i], L.moff[s1] - L.moff[s0])) continue;
+            const int pw = L.moff[s1] - L.moff[s0];
+            if (ragged_flat(s1 - s0, L.kv[i], pw)) {
+                int c = 0;
+                while (((long long)pw * L.kv[i]) >> (c + 1)) ++c;
+                by_work[c].push_back((int)i);
+                continue;
+            }
             for (int s = s0; s < s1; ++s) {
                 L.heavy.push_back(s);
                 L.heavy.push_back((int)i);
             }
         }
+        for (int c = 31; c >= 0; --c)
+            for (int i : by_work[c]) {
+                const int s0 = L.node_ptr[i], s1 = L.node_ptr[i + 1];
+                const int rec[8] = {s0,         s1 - s0, L.kv[i], L.uoff[i], L.moff[s0],
+                                    L.moff[s1] - L.moff[s0], i,
+                                    (1 << 20) / L.kv[i] + 1};
+                L.vrec.insert(L.vrec.end(), rec, rec + 8);
+                if ((1ll << c) >= ragged_wide_work(N)) ++L.num_wide;
+            }
         L.coff.assign((size_t)E + 1, 0);
         for (long long c = 0; c < E; ++c) L.coff[c + 1] = L.coff[c] + L.kv[cdst(c)];
         L.unary.resize((size_t)L.belief_floats);
@@ -625,12 +650,14 @@ int create_graph_from_layout(HostLayout& layout, const bp_graph_desc* desc, bp_g
         if (n == 0) return hipSuccess;
         return hipMemcpyAsync(g->base + o, p, n, hipMemcpyHostToDevice, s);
     };
-    hipError_t errs[17] = {
+    const hipError_t errs[] = {
         up(g->off.kv, L.kv.data(), sizeof(int) * L.kv.size()),
         up(g->off.uoff, L.uoff.data(), sizeof(int) * L.uoff.size()),
         up(g->off.moff, L.moff.data(), sizeof(int) * L.moff.size()),
         up(g->off.toff, L.toff.data(), sizeof(int) * L.toff.size()),
         up(g->off.heavy, L.heavy.data(), sizeof(int) * L.heavy.size()),
+        up(g->off.vrec, L.vrec.data(), sizeof(int) * L.vrec.size()),
+        up(g->off.rin, L.rin.data(), sizeof(int) * L.rin.size()),
         up(g->off.rev16, L.rev16.data(), sizeof(short) * L.rev16.size()),
         up(g->off.tile_slot, L.tile_slot.data(), sizeof(int) * L.tile_slot.size()),
         up(g->off.tiles4, L.tiles4.data(), sizeof(int) * L.tiles4.size()),
@@ -748,11 +775,16 @@ static EvalArgs run_args(const bp_graph* g, int schedule, double eps, double p, 
     a.toff = g->at<int>(g->off.toff);
     a.heavy = g->at<int>(g->off.heavy);
     a.num_heavy = (int)(L.heavy.size() / 2);
+    a.vrec = g->at<int>(g->off.vrec);
+    a.num_flat = (int)(L.vrec.size() / 8);
+    a.num_wide = L.num_wide;
+    a.rin = g->at<int>(g->off.rin);
     if (L.layout == kLayoutRagged) {
-        // a wave per heavy slot and per variable, grid-stride: at most 8
-        // blocks per CU
-        const long long waves = (long long)L.N + a.num_heavy;
-        const long long blocks = (waves + kBlock / 64 - 1) / (kBlock / 64);
+        // a wave per heavy slot, a block per wide variable, a wave per other one,
+        // grid-stride: at most 8 blocks per CU
+        constexpr int W = kBlock / 64;
+        const long long blocks = (a.num_heavy + W - 1) / W + a.num_wide +
+                                 (a.num_flat - a.num_wide + W - 1) / W;
         a.pipe_grid = (int)std::max<long long>(
             1, std::min<long long>(blocks, 8ll * std::max(g->num_cus, 1)));
     }
@@ -1365,7 +1397,7 @@ int bp_marginals_device(bp_graph* g, float* out_device) {
         a.unary = g->at<float>(g->off.unary);
         a.kv = g->at<int>(g->off.kv);
         a.uoff = g->at<int>(g->off.uoff);
-        a.moff = g->at<int>(g->off.moff);
+        a.rin = g->at<int>(g->off.rin);
         a.in_buf[0] = g->cur();
         a.num_nodes = L.N;
         HIP_OK(launch_marginals_ragged(a, out_device, g->stream), "marginals kernel");

@@ -57,6 +57,15 @@ constexpr int kRaggedMaxDeg = 64;
 #define BP_RAGGED_HEAVY_WORK 16384
 #endif
 constexpr int kRaggedHeavyWork = BP_RAGGED_HEAVY_WORK;
+// A variable that is not heavy takes a block instead of a wave from this product
+// work on (P K_i; a power of two, a class of the work order), if the graph has
+// too few variables to give every wave slot of the device one (4,096 at four waves
+// per SIMD).  Microseconds per sweep with blocks from 1,024, 4,096 and never: 100
+// variables of mean degree 9: 21, 25, 38; 2,000 (degree 8): 37, 29, 42; 8,000: 79,
+// 64, 57.
+inline int ragged_wide_work(long long variables) {
+    return variables <= 1024 ? 1024 : variables <= 4096 ? 4096 : 1 << 30;
+}
 __host__ __device__ inline bool ragged_flat(int deg, int ki, int p) {
     return deg <= kRaggedMaxDeg && deg * ki <= kRaggedFlat && p <= kRaggedFlat &&
            p * ki <= kRaggedHeavyWork;
@@ -145,6 +154,13 @@ struct EvalArgs {
     const int* toff;            // [E+1] first table entry of each slot (K_i x K_j, x_i major)
     const int* heavy;           // [num_heavy][2] {slot, source} of the slots of heavy variables
     int num_heavy;
+    const int* vrec;            // [num_flat][8] {first slot, degree, K_i, first unary, first
+                                // message entry, message entries, variable, 2^20 / K_i + 1 (e / K_i
+                                // = e times it >> 20 for e < 8192)} of the variables
+                                // that are not heavy, by work
+    int num_flat;
+    int num_wide;               // the first records, each of which takes a block
+    const int* rin;             // [E] first message entry of the reverse slot
     const float* in_buf[2];     // m^t: candidates chosen by p_{t-1} (both equal on a run's first launch)
     float* out_buf[2];          // m^{t+1} under the larger [0] and smaller [1] keep threshold
     float* cand;                // RBP candidates, same layout as m

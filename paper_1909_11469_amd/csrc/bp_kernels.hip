@@ -26,6 +26,8 @@
 // committed state under both keep thresholds (two output buffers); the next
 // launch computes p_t from the finished counters in its prologue and reads the
 // matching buffer.  No pass over the messages is needed between iterations.
+#include <type_traits>
+
 #include "bp_internal.h"
 
 namespace bp {
@@ -2168,9 +2170,15 @@ __global__ void k_marginals_logodds(const int* node_ptr, const int* rev, const f
 
 // Wave-wide max and sum (every lane gets the result).
 __device__ __forceinline__ float wave_max_f(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    const int id = __float_as_int(-INFINITY);
+    auto step = [&](float x, int moved) { return fmaxf(x, __int_as_float(moved)); };
+    v = step(v, __builtin_amdgcn_update_dpp(id, __float_as_int(v), kRowShr1, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp(id, __float_as_int(v), kRowShr2, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp(id, __float_as_int(v), kRowShr4, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp(id, __float_as_int(v), kRowShr8, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp(id, __float_as_int(v), kRowBcast15, 0xA, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp(id, __float_as_int(v), kRowBcast31, 0xC, 0xF, false));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 __device__ __forceinline__ float wave_sum_f(float v) {
 #pragma unroll
@@ -2241,18 +2249,27 @@ __global__ void k_marginals_generic(const int* node_ptr, const int* rev, const f
 // entry, far below the ridge of the matrix cores and of the vector units, so
 // the vector units take it and the kernel is bound by the table traffic.
 //
-// One wave per source variable (grid-stride): lane x holds the aggregate of
-// states x and x + 64 (K_i <= 128); the cavity of each outgoing slot,
-// g(x_i) = exp(A(x_i) - log m_{j->i}(x_i) - max), goes to LDS.  Then every
-// (slot, target state) pair of the variable gets a lane, which takes the
-// product with its slot's table as a chain of fused multiply-adds over the
-// source states (the table entries of consecutive lanes are contiguous; a lane
-// runs four pairs together, 32 loads in flight); a lane per slot forms the normalisation, the
-// L-infinity residual and the frontier decision, and the pair lanes store the
-// committed values.  A heavy variable (slots over the wave's LDS, or much
-// product work: ragged_flat) gives each of its slots a wave of its own
-// (ragged_slot), taken before the other variables, so the launch is not held
-// up by one wave that runs a long chain of table loads.
+// One wave per source variable (grid-stride over records ordered by work, the
+// largest first): lane x holds the aggregate of states x and x + 64 (K_i <= 128);
+// the cavity of each outgoing slot, g(x_i) = exp(A(x_i) - log m_{j->i}(x_i) - max),
+// goes to LDS.  Then every (slot, target state) pair of the variable gets a lane,
+// which takes the product with its slot's table as a chain of fused multiply-adds
+// over the source states (the table entries of consecutive lanes are contiguous; a
+// lane runs four pairs together, 32 loads in flight); a lane per slot forms the
+// normalisation and the frontier decision, the pair lanes the change and the
+// committed values.
+//
+// What bounds a wave is its chain of dependent steps, so: everything a variable
+// needs to know comes in one record and its slots' offsets in one load each (row
+// of the incoming message, table, outputs); the first table entries, which depend
+// on no message, are requested before the incoming rows; the slot of a pair is one
+// LDS byte; maxima over the wave go through DPP; a slot's sum reads eight outputs
+// at a time; its largest change is an LDS integer maximum.  8,000 variables, mean
+// degree 8, 2..81 states: 106 -> 46 us per sweep (116 MB of tables: 25 us at
+// the rate of a copy).  A heavy variable (slots over the wave's LDS, or much product
+// work: ragged_flat) gives each of its slots a wave of its own (ragged_slot),
+// taken before the other variables, so the launch is not held up by one wave that
+// runs a long chain of table loads.
 // ---------------------------------------------------------------------------
 
 // Wave-local LDS hand-off: this wave's LDS stores are complete and visible to
@@ -2295,14 +2312,14 @@ __device__ __forceinline__ void ragged_slot(const EvalArgs& a, const float* __re
     const float* U = a.unary + a.uoff[i];
     const int mo = a.moff[s], Kj = a.moff[s + 1] - mo;
     const float* __restrict__ T = a.pair + a.toff[s];
-    const int rj = a.moff[a.rev[s]];
+    const int rj = a.rin[s];
     const bool y0 = lane < Kj, y1 = lane + 64 < Kj;
     const float old0 = y0 ? m_in[mo + lane] : 0.0f;
     const float old1 = y1 ? m_in[mo + lane + 64] : 0.0f;
     float A0 = x0 ? U[lane] : 0.0f, A1 = x1 ? U[lane + 64] : 0.0f;
     for (int b = s0; b < s1; b += 64) {
         const int nb = min(64, s1 - b);
-        const int my_rin = lane < nb ? a.moff[a.rev[b + lane]] : 0;
+        const int my_rin = lane < nb ? a.rin[b + lane] : 0;
         for (int k0 = 0; k0 < nb; k0 += 8) {
             float v0[8], v1[8];
 #pragma unroll
@@ -2341,20 +2358,20 @@ __device__ __forceinline__ void ragged_slot(const EvalArgs& a, const float* __re
         const int steps = (Ki + R - 1) / R;
         float acc = 0.0f;
         int st = 0;
-        for (; st + 8 <= steps; st += 8) {
-            float tv[8], gv[8];
+        for (; st + 16 <= steps; st += 16) {
+            float tv[16], gv[16];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < 16; ++u) {
                 const int x = (st + u) * R + r;
                 const bool ok = lane < RK && x < Ki;
                 tv[u] = ok ? T[(st + u) * RK + lane] : 0.0f;
                 gv[u] = ok ? G[x] : 0.0f;
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc = fmaf(tv[u], gv[u], acc);
+            for (int u = 0; u < 16; ++u) acc = fmaf(tv[u], gv[u], acc);
         }
-        if (st < steps) {
-            // the remaining steps (fewer than eight), predicated, loads together
+        for (; st < steps; st += 8) {
+            // the remaining steps, predicated, eight loads together
             float tv[8], gv[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -2426,176 +2443,297 @@ __device__ __forceinline__ void ragged_slot(const EvalArgs& a, const float* __re
     wave_lds_sync();  // G and Cv are free for the wave's next slot
 }
 
-// Four waves per SIMD: 124 to 127 registers, none spilled (three waves and up
-// to 141 registers unconstrained).
+// The LDS of one wave of the flat path (four blocks of four waves per CU).
+struct RaggedLds {
+    float G[kRaggedFlat];                  // logs, then cavity vectors, slot-major; then old values
+    float C[kRaggedFlat];                  // aggregate; then outputs of the variable's slots
+    unsigned char slot[kRaggedFlat];       // slot of an output
+    int toff[kRaggedMaxDeg];               // table of the slot
+    union {
+        int rin[kRaggedMaxDeg];            // row of the message into the variable
+        float inv[kRaggedMaxDeg];          // 1 / z
+    };
+    unsigned int r[kRaggedMaxDeg];         // residual bits, then the keep decisions
+    unsigned short off[kRaggedMaxDeg + 1]; // first output of the slot
+};
+static_assert(kRaggedMaxDeg <= 64, "a lane per slot");
+
+// Largest value of each row of 16 lanes, in all of them.
+__device__ __forceinline__ float row_max_f(float v) {
+    auto ror = [](float x, auto ctrl) {
+        return __int_as_float(
+            __builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, false));
+    };
+    v = fmaxf(v, ror(v, std::integral_constant<int, 0x128>{}));  // row_ror 8, 4, 2, 1
+    v = fmaxf(v, ror(v, std::integral_constant<int, 0x124>{}));
+    v = fmaxf(v, ror(v, std::integral_constant<int, 0x122>{}));
+    return fmaxf(v, ror(v, std::integral_constant<int, 0x121>{}));
+}
+
+// One variable (record f) on NW waves: a wave of its own, or the whole block.
+template <int MODE, int NW>
+__device__ __forceinline__ void ragged_var(const EvalArgs& a, const float* __restrict__ m_in, int f,
+                                           RaggedLds& l, float& rmax, unsigned int& act,
+                                           unsigned int& sa, unsigned int& sb) {
+    constexpr int NT = 64 * NW;
+    constexpr int PJ = NW == 1 ? 4 : 2, XS = 32 / PJ;  // pairs of a lane, states per step
+    const int lane = threadIdx.x & 63;
+    const int wv = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lid = 64 * wv + lane;  // lane of the group
+    auto sync = [&]() {
+        if (NW == 1)
+            wave_lds_sync();
+        else
+            lds_barrier();
+    };
+    const int4 va = ((const int4*)a.vrec)[2 * f], vb = ((const int4*)a.vrec)[2 * f + 1];
+    const int s0 = __builtin_amdgcn_readfirstlane(va.x), deg = __builtin_amdgcn_readfirstlane(va.y);
+    const int Ki = __builtin_amdgcn_readfirstlane(va.z), uo = __builtin_amdgcn_readfirstlane(va.w);
+    const int mo0 = __builtin_amdgcn_readfirstlane(vb.x), P = __builtin_amdgcn_readfirstlane(vb.y);
+    const int i = __builtin_amdgcn_readfirstlane(vb.z);
+    const unsigned int magic = (unsigned int)__builtin_amdgcn_readfirstlane(vb.w);
+    if (deg == 0) return;
+    const float* U = a.unary + uo;
+    const float fK = (float)Ki;  // log(K_i m) keeps the aggregate near zero
+    const bool x0 = lane < Ki, x1 = lane + 64 < Ki;
+    // a lane per slot: the row of the message into the variable, the table,
+    // the first output
+    const int sl = s0 + min(lane, deg - 1);
+    const int rin_k = a.rin[sl];
+    const int to_k = a.toff[sl];
+    const int off_k = lane < deg ? a.moff[sl] - mo0 : P;
+    float A0 = x0 ? U[lane] : 0.0f, A1 = x1 ? U[lane + 64] : 0.0f;
+    if (lid <= deg && lid < 64) l.off[lid] = (unsigned short)off_k;
+    if (lid == 0) l.off[deg] = (unsigned short)P;
+    if (lid < deg) {
+        l.rin[lid] = rin_k;
+        l.toff[lid] = to_k;
+        l.r[lid] = 0u;
+    }
+    for (int k = wv; k < deg; k += NW) {
+        const int o = __builtin_amdgcn_readlane(off_k, k);
+        const int e = k + 1 < deg ? __builtin_amdgcn_readlane(off_k, min(k + 1, 63)) : P;
+        for (int q = o + lane; q < e; q += 64) l.slot[q] = (unsigned char)k;
+    }
+    sync();
+    // the pairs of a lane: PJ, NT apart, of each PJ NT (a wave skips what lies past P)
+    const float* T[PJ];
+    const float* g[PJ];
+    int Kj[PJ];
+    float tv[PJ][XS];
+    auto pairs = [&](int pb) {
+#pragma unroll
+        for (int j = 0; j < PJ; ++j) {
+            const int pp = min(pb + lid + NT * j, P - 1);
+            const int k = l.slot[pp];
+            const int o = l.off[k];
+            Kj[j] = l.off[k + 1] - o;
+            T[j] = a.pair + l.toff[k] + (pp - o);
+            g[j] = l.G + k * Ki;
+        }
+    };
+    // table rows x .. x + XS - 1 of every pair (rows past the last: the last again)
+    auto load_tables = [&](int pb, int x) {
+        if (x + XS <= Ki) {
+#pragma unroll
+            for (int j = 0; j < PJ; ++j) {
+                if (pb + 64 * wv + NT * j >= P) break;
+                const float* t = T[j] + x * Kj[j];
+#pragma unroll
+                for (int u = 0; u < XS; ++u) {
+                    tv[j][u] = *t;
+                    t += Kj[j];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < PJ; ++j) {
+                if (pb + 64 * wv + NT * j >= P) break;
+#pragma unroll
+                for (int u = 0; u < XS; ++u) tv[j][u] = T[j][min(x + u, Ki - 1) * Kj[j]];
+            }
+        }
+    };
+    pairs(0);
+    load_tables(0, 0);
+    // logs of the incoming rows, lane by entry: slot q = e / K_i, state e - q K_i
+    const int DK = deg * Ki;
+    constexpr int RU = NW == 1 ? 4 : 2;
+    for (int e0 = 0; e0 < DK; e0 += RU * NT) {
+        float v[RU];
+#pragma unroll
+        for (int j = 0; j < RU; ++j) {
+            const int e = min(e0 + lid + NT * j, DK - 1);
+            const int q = (int)(((unsigned int)e * magic) >> 20);
+            v[j] = m_in[l.rin[q] + (e - q * Ki)];
+        }
+#pragma unroll
+        for (int j = 0; j < RU; ++j) v[j] *= fK;
+        log_batch<RU>(v);
+#pragma unroll
+        for (int j = 0; j < RU; ++j) {
+            const int e = e0 + lid + NT * j;
+            if (e < DK) l.G[e] = v[j];
+        }
+    }
+    sync();
+    // the aggregate, in slot order
+    if (wv == 0) {
+        for (int k0 = 0; k0 < deg; k0 += 8) {
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = l.G[min(k0 + j, deg - 1) * Ki + min(lane, Ki - 1)];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (k0 + j < deg) A0 += v[j];
+            if (Ki > 64) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    v[j] = l.G[min(k0 + j, deg - 1) * Ki + min(lane + 64, Ki - 1)];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (k0 + j < deg) A1 += v[j];
+            }
+        }
+        if (x0) l.C[lane] = A0;
+        if (x1) l.C[lane + 64] = A1;
+    }
+    sync();
+    // the cavities, W lanes per slot (K_i rounded up to 16, 32 or 64)
+    {
+        const int wl = Ki <= 16 ? 4 : Ki <= 32 ? 5 : 6;
+        const int x = lid & ((1 << wl) - 1);
+        for (int k = lid >> wl; k < deg; k += NT >> wl) {
+            float* G = l.G + k * Ki;
+            const float c0 = x < Ki ? l.C[x] - G[x] : -INFINITY;
+            const float c1 = Ki > 64 && x + 64 < Ki ? l.C[x + 64] - G[x + 64] : -INFINITY;
+            float mx = row_max_f(fmaxf(c0, c1));
+            if (wl > 4) mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+            if (wl > 5) mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            if (x < Ki) G[x] = expf(c0 - mx);
+            if (Ki > 64 && x + 64 < Ki) G[x + 64] = expf(c1 - mx);
+        }
+    }
+    sync();
+    for (int pb = 0; pb < P; pb += PJ * NT) {
+        if (pb) {
+            pairs(pb);
+            load_tables(pb, 0);
+        }
+        float acc[PJ];
+#pragma unroll
+        for (int j = 0; j < PJ; ++j) acc[j] = 0.0f;
+        // XS source states per step, the last step cut short
+        for (int x = 0; x < Ki; x += XS) {
+            if (x) load_tables(pb, x);
+            if (x + XS <= Ki) {
+#pragma unroll
+                for (int j = 0; j < PJ; ++j) {
+                    if (pb + 64 * wv + NT * j >= P) break;
+#pragma unroll
+                    for (int u = 0; u < XS; ++u) acc[j] = fmaf(tv[j][u], g[j][x + u], acc[j]);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < XS - 1; ++u) {
+                    if (x + u >= Ki) break;
+#pragma unroll
+                    for (int j = 0; j < PJ; ++j) acc[j] = fmaf(tv[j][u], g[j][x + u], acc[j]);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < PJ; ++j)
+            if (pb + lid + NT * j < P) l.C[pb + lid + NT * j] = acc[j];
+    }
+    sync();
+    if (lid < deg) {
+        const int o = l.off[lid], n = l.off[lid + 1] - o;
+        float z = 0.0f;
+        for (int q = 0; q < n; q += 8) {
+            float c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c[u] = l.C[o + min(q + u, n - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) z += q + u < n ? c[u] : 0.0f;
+        }
+        l.inv[lid] = 1.0f / z;
+    }
+    sync();
+    // normalised outputs back into C, old values into G (the cavities are
+    // done), the largest change of each slot
+    for (int pb = 0; pb < P; pb += PJ * NT) {
+        float old[PJ];
+#pragma unroll
+        for (int j = 0; j < PJ; ++j) old[j] = m_in[mo0 + min(pb + lid + NT * j, P - 1)];
+#pragma unroll
+        for (int j = 0; j < PJ; ++j) {
+            const int p = pb + lid + NT * j;
+            if (p >= P) continue;
+            const int k = l.slot[p];
+            const float v = l.C[p] * l.inv[k];
+            l.C[p] = v;
+            const float d = fabsf(v - old[j]);
+            if (d > 0.0f) atomicMax(&l.r[k], __float_as_uint(d));  // (not for NaN)
+            if (MODE == kModeRnBP) l.G[p] = old[j];
+        }
+    }
+    sync();
+    if (lid < deg) {
+        const float r = __uint_as_float(l.r[lid]);
+        const bool active = r > a.eps;
+        bool ka = false, kb = false;
+        if (MODE == kModeRnBP && active) {
+            const unsigned int u24 = draw24(a, i, lid);
+            ka = u24 < a.thr_a;
+            kb = u24 < a.thr_b;
+        }
+        if (MODE == kModeRBP) a.keys[s0 + lid] = __float_as_uint(r);
+        l.r[lid] = (ka ? 1u : 0u) | (kb ? 2u : 0u);
+        act += active;
+        sa += ka;
+        sb += kb;
+        rmax = fmaxf(rmax, r);
+    }
+    if (MODE == kModeRnBP) sync();
+    if (MODE != kModeEvalOnly) {
+        for (int p = lid; p < P; p += NT) {
+            const unsigned int kp = MODE == kModeRnBP ? l.r[l.slot[p]] : 0u;
+            ragged_commit<MODE>(a, mo0 + p, l.C[p], MODE == kModeRnBP ? l.G[p] : 0.0f, kp & 1u,
+                                kp & 2u);
+        }
+    }
+    sync();  // the LDS is free for the next variable
+}
+
 template <int MODE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_ragged(
     EvalArgs a) {
     __shared__ RedScratch red;
     __shared__ unsigned long long s_red[2];
-    __shared__ float s_g[kBlock / 64][kRaggedFlat];    // cavity vectors, slot-major
-    __shared__ float s_c[kBlock / 64][kRaggedFlat];    // outputs of the variable's slots
-    __shared__ int s_off[kBlock / 64][kRaggedMaxDeg + 1];
-    __shared__ int s_rin[kBlock / 64][kRaggedMaxDeg];    // row of the message into the variable
-    __shared__ int s_toff[kBlock / 64][kRaggedMaxDeg];   // table of the slot
-    __shared__ float s_inv[kBlock / 64][kRaggedMaxDeg];
-    __shared__ unsigned int s_keep[kBlock / 64][kRaggedMaxDeg];
+    __shared__ RaggedLds s_l[kBlock / 64];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const float* __restrict__ m_in = iteration_prologue(a, s_red, blockIdx.x == 0);
     if (!m_in) return;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    float* G = s_g[w];
-    float* Cv = s_c[w];
-    int* off = s_off[w];
-    const int waves = (int)(gridDim.x * (blockDim.x >> 6));
     float rmax = 0.0f;
     unsigned int act = 0, sa = 0, sb = 0;
-    const int gw = (int)(blockIdx.x * (blockDim.x >> 6) + w);
-    for (int h = gw; h < a.num_heavy; h += waves)
-        ragged_slot<MODE>(a, m_in, a.heavy[2 * h], a.heavy[2 * h + 1], G, Cv, rmax, act, sa, sb);
-    for (int i = gw; i < a.num_nodes; i += waves) {
-        const int Ki = a.kv[i];
-        const int s0 = a.node_ptr[i], s1 = a.node_ptr[i + 1];
-        const int deg = s1 - s0;
-        const float* U = a.unary + a.uoff[i];
-        const float fK = (float)Ki;  // log(K_i m) keeps the aggregate near zero
-        const bool x0 = lane < Ki, x1 = lane + 64 < Ki;
-        float A0 = x0 ? U[lane] : 0.0f, A1 = x1 ? U[lane + 64] : 0.0f;
-        const int mo0 = a.moff[s0];
-        const int P = a.moff[s1] - mo0;  // outputs of all slots of the variable
-        if (!ragged_flat(deg, Ki, P)) continue;  // a heavy variable: its slots are done
-        {
-            // Flat path.  A lane per slot fetches the slot's offsets (all in
-            // flight at once); the incoming rows are loaded eight slots at a
-            // time and their logs kept in LDS for the cavities; then the
-            // outputs of all slots at once (a lane per (slot, target state)
-            // pair), the per-slot sums, residuals and frontier decisions (a
-            // lane per slot), and the stores.
-            for (int k = lane; k < deg; k += 64) {
-                s_rin[w][k] = a.moff[a.rev[s0 + k]];
-                s_toff[w][k] = a.toff[s0 + k];
-                off[k] = a.moff[s0 + k] - mo0;
-            }
-            if (lane == 0) off[deg] = P;
-            wave_lds_sync();
-            for (int k0 = 0; k0 < deg; k0 += 8) {
-                float v0[8], v1[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int k = min(k0 + j, deg - 1);
-                    const int rin = s_rin[w][k];
-                    v0[j] = x0 ? m_in[rin + lane] : 1.0f;
-                    v1[j] = x1 ? m_in[rin + lane + 64] : 1.0f;
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) v0[j] *= fK;
-                log_batch<8>(v0);
-                if (Ki > 64) {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) v1[j] *= fK;
-                    log_batch<8>(v1);
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    if (k0 + j >= deg) break;
-                    const float l0 = v0[j], l1 = v1[j];
-                    if (x0) {
-                        A0 += l0;
-                        G[(k0 + j) * Ki + lane] = l0;
-                    }
-                    if (x1) {
-                        A1 += l1;
-                        G[(k0 + j) * Ki + lane + 64] = l1;
-                    }
-                }
-            }
-            wave_lds_sync();
-            for (int k = 0; k < deg; ++k) {
-                const float c0 = x0 ? A0 - G[k * Ki + lane] : -INFINITY;
-                const float c1 = x1 ? A1 - G[k * Ki + lane + 64] : -INFINITY;
-                const float mx = wave_max_f(fmaxf(c0, c1));
-                if (x0) G[k * Ki + lane] = expf(c0 - mx);
-                if (x1) G[k * Ki + lane + 64] = expf(c1 - mx);
-            }
-            wave_lds_sync();
-            // up to four pairs per lane at once (p, p + 64, p + 128, p + 192):
-            // their table loads are independent, so 4 x 8 are in flight
-            for (int pb = 0; pb < P; pb += 256) {
-                const float* T[4];
-                const float* g[4];
-                int Kj[4];
-                bool on[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int p = pb + lane + 64 * j;
-                    on[j] = p < P;
-                    const int pp = on[j] ? p : P - 1;
-                    int k = 0;
-                    while (off[k + 1] <= pp) ++k;
-                    Kj[j] = off[k + 1] - off[k];
-                    T[j] = a.pair + s_toff[w][k] + (pp - off[k]);
-                    g[j] = G + k * Ki;
-                }
-                float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                // eight source states per step, the last step predicated (a
-                // variable with few states takes one step, not one per state)
-                for (int x = 0; x < Ki; x += 8) {
-                    float tv[4][8];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) tv[j][u] = x + u < Ki ? T[j][(x + u) * Kj[j]] : 0.0f;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-#pragma unroll
-                        for (int u = 0; u < 8; ++u)
-                            if (x + u < Ki) acc[j] = fmaf(tv[j][u], g[j][x + u], acc[j]);
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (on[j]) Cv[pb + lane + 64 * j] = acc[j];
-            }
-            wave_lds_sync();
-            for (int k = lane; k < deg; k += 64) {
-                float z = 0.0f;
-                for (int q = off[k]; q < off[k + 1]; ++q) z += Cv[q];
-                s_inv[w][k] = 1.0f / z;
-            }
-            wave_lds_sync();
-            // normalised outputs back into Cv, |change| into G (cavities are done)
-            for (int p = lane; p < P; p += 64) {
-                int k = 0;
-                while (off[k + 1] <= p) ++k;
-                const float v = Cv[p] * s_inv[w][k];
-                Cv[p] = v;
-                G[p] = fabsf(v - m_in[mo0 + p]);
-            }
-            wave_lds_sync();
-            for (int k = lane; k < deg; k += 64) {
-                float r = 0.0f;
-                for (int q = off[k]; q < off[k + 1]; ++q) r = fmaxf(r, G[q]);
-                const bool active = r > a.eps;
-                bool ka = false, kb = false;
-                if (MODE == kModeRnBP && active) {
-                    const unsigned int u24 = draw24(a, i, k);
-                    ka = u24 < a.thr_a;
-                    kb = u24 < a.thr_b;
-                }
-                if (MODE == kModeRBP) a.keys[s0 + k] = __float_as_uint(r);
-                s_keep[w][k] = (ka ? 1u : 0u) | (kb ? 2u : 0u);
-                act += active;
-                sa += ka;
-                sb += kb;
-                rmax = fmaxf(rmax, r);
-            }
-            wave_lds_sync();
-            for (int p = lane; p < P; p += 64) {
-                int k = 0;
-                while (off[k + 1] <= p) ++k;
-                const unsigned int kp = s_keep[w][k];
-                const float old = MODE == kModeRnBP ? m_in[mo0 + p] : 0.0f;
-                ragged_commit<MODE>(a, mo0 + p, Cv[p], old, kp & 1u, kp & 2u);
-            }
-            wave_lds_sync();  // the wave's LDS is free for its next variable
+    // work items in turn over the blocks: four heavy slots, or one wide variable, or
+    // four other variables
+    constexpr int W = kBlock / 64;
+    const int nh = (a.num_heavy + W - 1) / W, nw = a.num_wide;
+    const int items = nh + nw + (a.num_flat - nw + W - 1) / W;
+    for (int it = blockIdx.x; it < items; it += gridDim.x) {
+        if (it < nh) {
+            const int h = it * W + w;
+            if (h < a.num_heavy)
+                ragged_slot<MODE>(a, m_in, a.heavy[2 * h], a.heavy[2 * h + 1], s_l[w].G, s_l[w].C,
+                                  rmax, act, sa, sb);
+        } else if (it < nh + nw) {
+            lds_barrier();  // the waves of the block leave their own variables
+            ragged_var<MODE, W>(a, m_in, it - nh, s_l[0], rmax, act, sa, sb);
+        } else {
+            const int f = nw + (it - nh - nw) * W + w;
+            if (f < a.num_flat) ragged_var<MODE, 1>(a, m_in, f, s_l[w], rmax, act, sa, sb);
         }
     }
     block_accumulate(&red, a.ctr, a.t, rmax, act, sa, sb);
@@ -2614,7 +2752,7 @@ __global__ __launch_bounds__(kBlock) void k_marginals_ragged(EvalArgs a, float* 
         const bool x0 = lane < Ki, x1 = lane + 64 < Ki;
         float A0 = x0 ? U[lane] : -INFINITY, A1 = x1 ? U[lane + 64] : -INFINITY;
         for (int s = a.node_ptr[i]; s < a.node_ptr[i + 1]; ++s) {
-            const int rin = a.moff[a.rev[s]];
+            const int rin = a.rin[s];
             if (x0) A0 += logf(fK * m[rin + lane]);
             if (x1) A1 += logf(fK * m[rin + lane + 64]);
         }
