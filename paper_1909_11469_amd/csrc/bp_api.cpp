@@ -1,8 +1,8 @@
 // C ABI of libbp (include/bp.h): validation, device layout, and the host side of
 // the Alg. 1 loop.  The loop itself runs on the device: each iteration is a
 // fixed sequence of kernel launches whose convergence test and EdgeRatio rule
-// read device counters, so the host only enqueues work and polls a flag every
-// check_every iterations.
+// read device counters, so the host only enqueues work, a few iterations ahead of
+// the progress word that the device writes to pinned memory.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -18,6 +18,8 @@
 #include <unordered_map>
 #include <unordered_set>
 #include <vector>
+
+#include <sched.h>
 
 #include "../../include/bp.h"
 #include "bp_internal.h"
@@ -531,6 +533,7 @@ struct bp_graph {
     long long t_next = 0;        // global iteration number of the next evaluation
     long long prev_active = -1;  // n_{t_next - 1}
     DevState* host_state = nullptr;  // pinned mirror
+    unsigned long long* prog = nullptr;  // pinned progress word of a run (EvalArgs::prog)
     hipEvent_t ev0 = nullptr, ev1 = nullptr;  // timing of a run (run_events)
     int num_cus = 0;                 // compute units of the device
     int resident[4] = {0, 0, 0, 0};  // log-odds eval blocks resident per CU, by mode
@@ -638,7 +641,10 @@ int create_graph_from_layout(HostLayout& layout, const bp_graph_desc* desc, bp_g
         }
         g->owns_memory = true;
     }
-    e = hipHostMalloc((void**)&g->host_state, sizeof(DevState), hipHostMallocDefault);
+    // the progress word on a cache line of its own behind the mirror
+    const size_t prog_off = (sizeof(DevState) + 127) & ~size_t(127);
+    e = hipHostMalloc((void**)&g->host_state, prog_off + 128, hipHostMallocDefault);
+    if (e == hipSuccess) g->prog = (unsigned long long*)((char*)g->host_state + prog_off);
     if (e != hipSuccess) {
         g->host_state = nullptr;
         return give_back(hip_fail(e, "hipHostMalloc"));
@@ -853,6 +859,24 @@ static hipError_t run_events(bp_graph* g) {
     if (!g->ev0) e = hipEventCreate(&g->ev0);
     if (e == hipSuccess && !g->ev1) e = hipEventCreate(&g->ev1);
     return e;
+}
+
+// Waits until `closed` evaluations of the run are closed or it has converged;
+// returns whether it has.  The stream is asked now and then, so that a failed
+// launch (whose error the next call returns) cannot keep the host here.
+static bool wait_progress(const bp_graph* g, hipStream_t s, unsigned long long closed) {
+    for (unsigned int spins = 1;; ++spins) {
+        const unsigned long long v = __atomic_load_n(g->prog, __ATOMIC_ACQUIRE);
+        if (v & 1) return true;
+        if ((v >> 1) >= closed) return false;
+        if (spins % 64 == 0) {
+            if (spins % 16384 == 0 && hipStreamQuery(s) != hipErrorNotReady) {
+                // nothing is running any more: what was reported is final
+                return (__atomic_load_n(g->prog, __ATOMIC_ACQUIRE) & 1) != 0;
+            }
+            sched_yield();
+        }
+    }
 }
 
 // A run of a small K = 2 graph (k_solve_small): launches of at most
@@ -1130,7 +1154,18 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
     int in_chunk = 0;
     long long it = 0;
     bool final_launched = false;
+    __atomic_store_n(g->prog, 0ull, __ATOMIC_RELEASE);
+    a.prog = g->prog;
     for (;; ++it) {
+        // The host follows the run by the progress word.  It polls by readback every
+        // check_every iterations instead where it needs the state at a fixed
+        // iteration: profiling, launch-shape tuning, the switch to sparse
+        // re-evaluation.
+        const bool follow = !prof_every && !tune && (o.sparse != 2 || sparse_now);
+        if (follow && it > kAhead && wait_progress(g, s, (unsigned long long)(it - kAhead))) {
+            --it;  // converged: nothing more to launch
+            break;
+        }
         const long long t = t_start + it;
         final_launched = it == o.max_iters;
         if (sparse_now) {
@@ -1157,14 +1192,14 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
             } else {
                 HIP_OK(launch_sparse_iteration(a, s), "sparse iteration");
             }
-            ++in_chunk;
-            if (in_chunk == o.check_every || final_launched) {
+            if (final_launched) break;
+            if (!follow && ++in_chunk == o.check_every) {
                 HIP_OK(hipMemcpyAsync(g->host_state, rs.st, kStateReadback, hipMemcpyDeviceToHost,
                                       s),
                        "state readback");
                 HIP_OK(hipStreamSynchronize(s), "synchronize");
                 in_chunk = 0;
-                if (g->host_state->done || final_launched) break;
+                if (g->host_state->done) break;
             }
             continue;
         }
@@ -1229,6 +1264,10 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
                                      L.layout == kLayoutRagged ? a.moff : nullptr, s),
                    "top-k commit");
         }
+        if (follow) {
+            if (final_launched) break;
+            continue;
+        }
         ++in_chunk;
         if (in_chunk == o.check_every || final_launched) {
             if (prof_window) HIP_OK(hipEventRecord(kev[1], s), "event record");
@@ -1275,10 +1314,7 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
                 a.t = (unsigned int)(t + 1);
                 a.it = it + 1;
                 a.after_final = 0;
-                HIP_OK(launch_close_run(a, s), "close evaluation");
-                HIP_OK(hipMemcpyAsync(g->host_state, rs.st, kStateReadback, hipMemcpyDeviceToHost,
-                                      s),
-                       "state readback");
+                HIP_OK(launch_close_run(a, g->host_state, kStateReadback, s), "close evaluation");
                 HIP_OK(hipStreamSynchronize(s), "synchronize");
                 if (g->host_state->done) break;
                 if (mode == kModeRBP) {
@@ -1298,16 +1334,16 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
     }
     if (sparse_now) {
         HIP_OK(launch_sparse_rmax(a, s), "max residual");
+        HIP_OK(hipMemcpyAsync(g->host_state, rs.st, kStateReadback, hipMemcpyDeviceToHost, s),
+               "state readback");
     } else {
         // close the last launched evaluation (a no-op if a later prologue already did)
         a.t = (unsigned int)(t_start + it + 1);
         a.it = it + 1;
         a.after_final = final_launched ? 1 : 0;
-        HIP_OK(launch_close_run(a, s), "close run");
+        HIP_OK(launch_close_run(a, g->host_state, kStateReadback, s), "close run");
     }
     if (ev1) HIP_OK(hipEventRecord(ev1, s), "event record");
-    HIP_OK(hipMemcpyAsync(g->host_state, rs.st, kStateReadback, hipMemcpyDeviceToHost, s),
-           "state readback");
     HIP_OK(hipStreamSynchronize(s), "synchronize");
     float total_ms = 0.0f;
     if (ev0) HIP_OK(hipEventElapsedTime(&total_ms, ev0, ev1), "event time");
@@ -1701,9 +1737,7 @@ int server_retire(bp_server* s, Request* r) {
     a.t = (unsigned int)(last_it + 1);
     a.it = last_it + 1;
     a.after_final = last_it == b.max_iters ? 1 : 0;
-    HIP_OK(launch_close_run(a, s->stream), "close run");
-    HIP_OK(hipMemcpyAsync(g->host_state, g->st(), kStateReadback, hipMemcpyDeviceToHost, s->stream),
-           "state readback");
+    HIP_OK(launch_close_run(a, g->host_state, kStateReadback, s->stream), "close run");
     HIP_OK(hipStreamSynchronize(s->stream), "synchronize");
     const DevState& st = *g->host_state;
     const bool converged = st.done != 0;

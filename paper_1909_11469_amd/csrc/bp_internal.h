@@ -73,6 +73,11 @@ __host__ __device__ inline bool ragged_flat(int deg, int ki, int p) {
 
 // 0: one log-odds value per message (K = 2 Ising); 1: K floats per message;
 // 2: K_j floats per message i -> j (per-variable state counts)
+// The progress word is written every so many closed evaluations, and the host keeps
+// at most kAhead launches ahead of what it says.
+constexpr unsigned long long kReportEvery = 4;
+constexpr long long kAhead = 8;
+
 enum Layout : int { kLayoutLogOdds = 0, kLayoutGeneric = 1, kLayoutRagged = 2 };
 enum PairDev : int { kPairIsing = 0, kPairShared = 1, kPairSharedAsym = 2, kPairDense = 3 };
 enum Mode : int { kModeLBP = 0, kModeRnBP = 1, kModeRBP = 2, kModeEvalOnly = 3 };
@@ -204,6 +209,7 @@ struct EvalArgs {
     unsigned char* dirty;       // [N] 1 if a message into the node was committed
     unsigned char* hasact;      // [N] 1 if a slot of the node has residual > eps
     int* dst;                   // [E] target node of each slot
+    unsigned long long* prog;   // pinned: evaluations closed << 1 | converged (or nullptr)
     int sp_first;               // first sparse iteration of a run (stored residuals invalid)
 };
 
@@ -260,7 +266,8 @@ hipError_t launch_batch_status(const BatchGraph* graphs, int num_graphs, unsigne
 hipError_t launch_init_state(DevState* st, CounterLine* ctr, hipStream_t s);
 hipError_t launch_fill(float* p, float v, long long n, hipStream_t s);
 hipError_t launch_eval(int layout, int mode, const EvalArgs& a, hipStream_t s);
-hipError_t launch_close_run(const EvalArgs& a, hipStream_t s);
+// host: pinned memory that takes the first `bytes` of the state, or nullptr
+hipError_t launch_close_run(const EvalArgs& a, void* host, size_t bytes, hipStream_t s);
 // fresh: start from uniform messages instead of msg.  mode: kModeLBP / RnBP / RBP.
 hipError_t launch_solve_small(int mode, const EvalArgs& a, float* msg, int fresh,
                               long long max_commits, SmallState* out, hipStream_t s);

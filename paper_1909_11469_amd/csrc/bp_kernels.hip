@@ -240,6 +240,18 @@ __device__ __forceinline__ int select_outcome(const EvalArgs& a, unsigned long l
     return (p_low == (a.low_is_a != 0)) ? 0 : 1;
 }
 
+// Tell the host how many evaluations of the run are closed and whether the last of
+// them converged: one word of pinned memory, so that the host can follow the run
+// (and stop launching) without a readback that leaves the device idle.  The store
+// crosses the bus while the block waits for it (about 2 us of its launch), so only
+// every kReportEvery-th count is reported, and convergence at once.
+__device__ __forceinline__ void report_progress(const EvalArgs& a, unsigned long long closed,
+                                                bool converged) {
+    if (a.prog && (converged || closed % kReportEvery == 0))
+        __hip_atomic_store(a.prog, closed << 1 | (converged ? 1ull : 0ull), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The counter lines the prologue needs, loaded by the 64 lanes of one wave
 // (lane c reads copy c): n of iterations t - 1 and t - 2, and for the block that
 // closes iteration t - 1 also its frontier sizes and max residual.
@@ -284,6 +296,7 @@ __device__ void wave_close(const EvalArgs& a, bool close, const CtrLoad& c,
     z->rmax = 0u;
     if (lane != 0) return;
     DevState* st = a.st;
+    report_progress(a, (unsigned long long)a.it, n1 == 0ull);
     const unsigned int tp = a.t - 1u;
     const int sel = select_outcome(a, n1, n2s);
     atomicAdd(&st->evaluated, a.num_messages);
@@ -2125,14 +2138,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
 }
 
 // Closes the last evaluation of a run (one wave): the same bookkeeping the
-// next evaluation's prologue would do.
-__global__ void k_close_run(EvalArgs a) {
-    if (a.st->done) return;
-    CtrLoad c;
-    ctr_load(a, true, c);
-    unsigned long long n1;
-    long long n2;
-    wave_close(a, true, c, n1, n2);
+// next evaluation's prologue would do.  With `host` (pinned memory) it also copies
+// the state's leading words there, which a readback would take a launch for.
+__global__ void k_close_run(EvalArgs a, unsigned int* host, int words) {
+    if (!a.st->done) {
+        CtrLoad c;
+        ctr_load(a, true, c);
+        unsigned long long n1;
+        long long n2;
+        wave_close(a, true, c, n1, n2);
+    }
+    if (!host) return;
+    __threadfence();  // lane 0's stores and adds, before the lanes read them from L2
+    const unsigned int* st = (const unsigned int*)a.st;
+    for (int i = threadIdx.x; i < words; i += 64)
+        host[i] = __hip_atomic_load(&st[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __global__ void k_init_state(DevState* st, CounterLine* ctr) {
@@ -2961,6 +2981,7 @@ __global__ __launch_bounds__(kBlock) void k_sparse_commit(EvalArgs a) {
             z->rmax = 0u;
             if (lane == 0) {
                 DevState* st = a.st;
+                report_progress(a, (unsigned long long)a.it + 1ull, n1 == 0ull);
                 atomicAdd(&st->evaluated, ev);
                 atomicAdd(&st->evals, 1ull);
                 if (cm_prev) atomicAdd(&st->committed, cm_prev);
@@ -3447,6 +3468,7 @@ __global__ void k_sparse_rbp_close(EvalArgs a) {
     z->sel_b = 0ull;
     z->rmax = 0u;
     if (lane != 0) return;
+    report_progress(a, (unsigned long long)a.it + 1ull, n1 == 0ull);
     atomicAdd(&st->evaluated, ev);
     atomicAdd(&st->evals, 1ull);
     st->sp_n[a.t & 3u] = n1;
@@ -4255,8 +4277,8 @@ hipError_t launch_solve_small(int mode, const EvalArgs& a, float* msg, int fresh
     return launch_small_nt<1024>(mode, a, msg, fresh, max_commits, out, s);
 }
 
-hipError_t launch_close_run(const EvalArgs& a, hipStream_t s) {
-    k_close_run<<<1, 64, 0, s>>>(a);
+hipError_t launch_close_run(const EvalArgs& a, void* host, size_t bytes, hipStream_t s) {
+    k_close_run<<<1, 64, 0, s>>>(a, (unsigned int*)host, (int)(bytes / sizeof(unsigned int)));
     return hipGetLastError();
 }
 
