@@ -172,6 +172,23 @@ bool positive_all(const double* p, size_t n) {
 // Validate the problem (Eq. (1): finite state sets, positive potentials) and
 // build the device layout: directed messages sorted by (source, target), the
 // reverse-slot index, per-slot parameters and node tiles.
+// The error of the first edge that is out of range, a self-loop, or equal to an
+// earlier one (build_layout has found that there is one).
+int report_bad_edge(const bp_graph_desc* d) {
+    const long long N = d->num_vars, M = d->num_edges;
+    std::unordered_set<unsigned long long> seen;
+    for (long long u = 0; u < M; ++u) {
+        const long long a = d->edges[2 * u], b = d->edges[2 * u + 1];
+        if (a < 0 || a >= N || b < 0 || b >= N)
+            return fail(BP_EINVAL, "edge %lld = (%lld, %lld) out of range", u, a, b);
+        if (a == b) return fail(BP_EINVAL, "edge %lld is a self-loop", u);
+        const unsigned long long key =
+            (unsigned long long)std::min(a, b) * (unsigned long long)N + std::max(a, b);
+        if (!seen.insert(key).second) return fail(BP_EINVAL, "edge %lld duplicates an earlier edge", u);
+    }
+    return fail(BP_EINVAL, "invalid edges");
+}
+
 int build_layout(const bp_graph_desc* d, HostLayout& L) {
     if (!d) return fail(BP_EINVAL, "desc is NULL");
     const long long N = d->num_vars, K = d->num_states, M = d->num_edges;
@@ -238,18 +255,11 @@ int build_layout(const bp_graph_desc* d, HostLayout& L) {
         return fail(BP_EINVAL, "unknown flags");
     L.no_mfma = (d->flags & BP_FLAG_NO_MATRIX_CORES) ? 1 : 0;
     L.mfma_bf16 = (d->flags & BP_FLAG_BF16_MATRIX_CORES) ? 1 : 0;
-    {
-        std::unordered_set<unsigned long long> seen;
-        seen.reserve((size_t)M * 2 + 1);
-        for (long long u = 0; u < M; ++u) {
-            const long long a = d->edges[2 * u], b = d->edges[2 * u + 1];
-            if (a < 0 || a >= N || b < 0 || b >= N)
-                return fail(BP_EINVAL, "edge %lld = (%lld, %lld) out of range", u, a, b);
-            if (a == b) return fail(BP_EINVAL, "edge %lld is a self-loop", u);
-            const unsigned long long key =
-                (unsigned long long)std::min(a, b) * (unsigned long long)N + std::max(a, b);
-            if (!seen.insert(key).second) return fail(BP_EINVAL, "edge %lld duplicates an earlier edge", u);
-        }
+    // The ends of every edge lie in range and differ.  (What is wrong is reported for
+    // the first edge at fault, by the scan of report_bad_edge.)
+    for (long long u = 0; u < M; ++u) {
+        const long long a = d->edges[2 * u], b = d->edges[2 * u + 1];
+        if (a < 0 || a >= N || b < 0 || b >= N || a == b) return report_bad_edge(d);
     }
 
     L.N = (int)N;
@@ -275,17 +285,22 @@ int build_layout(const bp_graph_desc* d, HostLayout& L) {
     // source: slot e holds m_{i->k}, the message its thread computes, so the
     // old value, the outputs and the per-slot constants are read and written
     // contiguously; the one gather is the incoming m_{k->i} at rev[e].
+    // Two counting passes: by target, then stably by source (a variable is the target
+    // of as many messages as it is the source of, so both use the same offsets).
     L.node_ptr.assign((size_t)N + 1, 0);
     for (long long c = 0; c < E; ++c) L.node_ptr[csrc(c) + 1]++;
     for (long long i = 0; i < N; ++i) L.node_ptr[i + 1] += L.node_ptr[i];
     std::vector<int> canon_of_slot((size_t)E);
     {
-        std::vector<int> fill(L.node_ptr.begin(), L.node_ptr.end() - 1);
-        for (long long c = 0; c < E; ++c) canon_of_slot[fill[csrc(c)]++] = (int)c;
+        std::vector<int> fill(L.node_ptr.begin(), L.node_ptr.end() - 1), by_dst((size_t)E);
+        for (long long c = 0; c < E; ++c) by_dst[fill[cdst(c)]++] = (int)c;
+        fill.assign(L.node_ptr.begin(), L.node_ptr.end() - 1);
+        for (long long q = 0; q < E; ++q) canon_of_slot[fill[csrc(by_dst[q])]++] = by_dst[q];
     }
+    // equal edges are neighbours now
     for (long long i = 0; i < N; ++i)
-        std::sort(canon_of_slot.begin() + L.node_ptr[i], canon_of_slot.begin() + L.node_ptr[i + 1],
-                  [&](int x, int y) { return cdst(x) < cdst(y); });
+        for (int q = L.node_ptr[i]; q + 1 < L.node_ptr[i + 1]; ++q)
+            if (cdst(canon_of_slot[q]) == cdst(canon_of_slot[q + 1])) return report_bad_edge(d);
     L.slot_of_canon.assign((size_t)E, 0);
     for (long long s = 0; s < E; ++s) L.slot_of_canon[canon_of_slot[s]] = (int)s;
     L.rev.resize((size_t)E);
