@@ -1925,7 +1925,7 @@ int bp_server_step(bp_server* s, int32_t launches, int32_t* finished) {
                 if (s->gexec) (void)hipGraphExecDestroy(s->gexec);
                 s->gexec = nullptr;
                 hipGraph_t gr = nullptr;
-                HIP_OK(batch_graph_nodes(graphs, s->max_graphs, list, ctl, grid, launches, &gr),
+                HIP_OK(batch_graph_nodes(graphs, list, ctl, grid, launches, &gr),
                        "record batched launches");
                 hipError_t e = hipGraphInstantiate(&s->gexec, gr, nullptr, nullptr, 0);
                 (void)hipGraphDestroy(gr);
@@ -1940,7 +1940,7 @@ int bp_server_step(bp_server* s, int32_t launches, int32_t* finished) {
             HIP_OK(hipGraphLaunch(s->gexec, s->stream), "replay batched launches");
         } else {
             for (int k = 0; k < launches; ++k)
-                HIP_OK(launch_eval_batch(graphs, s->max_graphs, list, ctl, grid, s->stream),
+                HIP_OK(launch_eval_batch(graphs, list, ctl, k, grid, s->stream),
                        "batch evaluation");
         }
         if (tuning >= 0) HIP_OK(hipEventRecord(s->ev1, s->stream), "event record");
@@ -1952,7 +1952,9 @@ int bp_server_step(bp_server* s, int32_t launches, int32_t* finished) {
     // retire the finished ones
     int n = 0;
     unsigned int* d_done = (unsigned int*)(s->base + s->done_off);
-    HIP_OK(launch_batch_status(graphs, s->max_graphs, d_done, s->stream), "batch status");
+    HIP_OK(launch_batch_status(graphs, s->max_graphs, d_done, ctl,
+                               blocks > 0 && launches > 0 ? launches : 0, s->stream),
+           "batch status");
     HIP_OK(hipMemcpyAsync(s->h_done, d_done, sizeof(unsigned int) * (size_t)s->max_graphs,
                           hipMemcpyDeviceToHost, s->stream),
            "status readback");

@@ -230,23 +230,20 @@ struct SmallState {
 };
 
 // One graph of a serving batch (device memory).  `a` holds the graph's
-// arguments as bp_run would set them; before every batched launch a small
-// kernel sets the per-launch fields (t, it, in_buf, out_buf, the mode of the
-// final evaluation) from the launch index.
+// arguments as bp_run would set them; a batched launch sets the per-launch fields
+// (t, it, in_buf, out_buf, the mode of the final evaluation) from its index.
 struct BatchGraph {
     EvalArgs a;
     float* msg[4];          // message buffer b of pair p at msg[2 p + b]
     long long first;        // global launch index of the graph's first evaluation
     long long max_iters;    // commits allowed; launch max_iters evaluates only
     int mode;               // kModeLBP or kModeRnBP
-    int mode_now;           // this launch: mode, or kModeEvalOnly for the final evaluation
-    int skip;               // this launch: 1 if the graph is not evaluated
-    int pad;
+    int pad[3];
 };
 
 // Control block of a server's batched launches (device memory): the index of
-// the next launch (read by k_batch_advance, advanced by the evaluation kernel,
-// so that recorded launch sequences can be replayed) and the tile-list length.
+// the next step's first launch (advanced after each step by k_batch_status, so
+// that recorded launch sequences can be replayed) and the tile-list length.
 struct BatchCtl {
     long long launch;
     int entries;
@@ -254,15 +251,16 @@ struct BatchCtl {
 };
 
 // Launch wrappers (bp_kernels.hip).  All return the hipError_t of the launch.
-// One batched iteration: k_batch_advance, then the persistent evaluation
+// One batched iteration, the step-th of its step: the persistent evaluation
 // kernel on `grid` blocks.
-hipError_t launch_eval_batch(BatchGraph* graphs, int num_graphs, const int* list, BatchCtl* ctl,
-                             int grid, hipStream_t s);
-// The same `launches` iterations as a HIP graph of kernel nodes only.
-hipError_t batch_graph_nodes(BatchGraph* graphs, int num_graphs, const int* list, BatchCtl* ctl,
+hipError_t launch_eval_batch(const BatchGraph* graphs, const int* list, const BatchCtl* ctl,
+                             int step, int grid, hipStream_t s);
+// The `launches` iterations of a step as a HIP graph of kernel nodes only.
+hipError_t batch_graph_nodes(const BatchGraph* graphs, const int* list, const BatchCtl* ctl,
                              int grid, int launches, hipGraph_t* out);
+// After a step of `launches` iterations: done flags, launch counter.
 hipError_t launch_batch_status(const BatchGraph* graphs, int num_graphs, unsigned int* done,
-                               hipStream_t s);
+                               BatchCtl* ctl, int launches, hipStream_t s);
 hipError_t launch_init_state(DevState* st, CounterLine* ctr, hipStream_t s);
 hipError_t launch_fill(float* p, float v, long long n, hipStream_t s);
 hipError_t launch_eval(int layout, int mode, const EvalArgs& a, hipStream_t s);

@@ -276,7 +276,7 @@ __device__ __forceinline__ void ctr_load(const EvalArgs& a, bool lead, CtrLoad& 
 // copies of t + 1.  The statistics are updated with stores and no-return
 // atomics, so nothing waits.  Returns n_{t-1} and n_{t-2} (the host's value
 // when t - 2 precedes the run).
-__device__ void wave_close(const EvalArgs& a, bool close, const CtrLoad& c,
+__device__ __forceinline__ void wave_close(const EvalArgs& a, bool close, const CtrLoad& c,
                            unsigned long long& n1_out, long long& n2_out) {
     const int lane = threadIdx.x & 63;
     // (counts of a launch are at most the number of messages, below 2^31)
@@ -338,6 +338,9 @@ __device__ __forceinline__ void prologue_issue(const EvalArgs& a, CtrLoad& c, bo
 __device__ __forceinline__ const float* prologue_finish(const EvalArgs& a, const CtrLoad& c,
                                                         unsigned long long* s_red,
                                                         bool lead) {
+    // (values, not an index: a local copy of the arguments stays in registers)
+    const float* const buf0 = a.in_buf[0];
+    const float* const buf1 = a.in_buf[1];
     if (a.it == 0) {
         if (lead && threadIdx.x < 64) {
             CounterLine* z = a.ctr + ((a.t + 1u) & 3u) * kCounterCopies + threadIdx.x;
@@ -347,7 +350,7 @@ __device__ __forceinline__ const float* prologue_finish(const EvalArgs& a, const
             z->rmax = 0u;
             if (threadIdx.x == 0) a.st->in_sel[a.t & 3u] = (unsigned int)a.sel0;
         }
-        return a.in_buf[0];
+        return buf0;
     }
     if (threadIdx.x < 64) {
         unsigned long long n1;
@@ -361,7 +364,7 @@ __device__ __forceinline__ const float* prologue_finish(const EvalArgs& a, const
     lds_barrier();
     const unsigned long long n1 = s_red[0];
     if (n1 == 0ull) return nullptr;
-    return a.in_buf[select_outcome(a, n1, (long long)s_red[1])];
+    return select_outcome(a, n1, (long long)s_red[1]) ? buf1 : buf0;
 }
 
 __device__ __forceinline__ const float* iteration_prologue(const EvalArgs& a,
@@ -768,26 +771,21 @@ __global__ __launch_bounds__(kBlock) void k_eval_logodds_big(EvalArgs a) {
 // software-pipelined tile loop as bp_run's kernel, then its oversized nodes.
 // ---------------------------------------------------------------------------
 
-// Before each batched launch: the per-launch fields of every graph's
-// arguments, as bp_run sets them for its iteration `it`.
-__global__ void k_batch_advance(BatchGraph* graphs, int num_graphs, const BatchCtl* ctl) {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= num_graphs) return;
-    const long long launch = ctl->launch;
-    BatchGraph& G = graphs[g];
-    const long long it = launch - G.first;
-    G.skip = (it < 0 || it > G.max_iters) ? 1 : 0;
-    if (G.skip) return;
-    EvalArgs& a = G.a;
+// The arguments of graph G for the launch with index `launch`: its per-launch fields
+// as bp_run sets them for its iteration it = launch - G.first.  (A kernel of its own
+// that stored them before every launch took 4.7 us of the launch's 32.)
+__device__ __forceinline__ EvalArgs batch_args(const BatchGraph& G, long long it) {
+    EvalArgs a = G.a;
     a.it = it;
     a.t = (unsigned int)it;
     a.after_final = 0;
+    a.prog = nullptr;
     const int pin = (int)(it & 1);
     a.in_buf[0] = it == 0 ? G.msg[0] : G.msg[2 * pin];
     a.in_buf[1] = it == 0 ? G.msg[0] : G.msg[2 * pin + 1];
     a.out_buf[0] = G.msg[2 * (pin ^ 1)];
     a.out_buf[1] = G.msg[2 * (pin ^ 1) + 1];
-    G.mode_now = it == G.max_iters ? kModeEvalOnly : G.mode;
+    return a;
 }
 
 // The regular tiles of one graph's run of list entries.
@@ -819,13 +817,14 @@ __device__ __forceinline__ void batch_run(const EvalArgs& a, const float* __rest
 
 __global__ __launch_bounds__(kBlockLO) void k_eval_batch(const BatchGraph* __restrict__ graphs,
                                                        const int4* __restrict__ list,
-                                                       BatchCtl* ctl) {
+                                                       const BatchCtl* __restrict__ ctl,
+                                                       int step) {
     __shared__ LogoddsLds l;
     __shared__ float s_part[kBlock / 64];
     __shared__ RedScratch red;
     __shared__ unsigned long long s_red[2];
-    // the next launch's index (k_batch_advance of this launch has read it)
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->launch += 1;
+    // `step`: the launch's number among those since the counter last advanced
+    const long long launch = ctl->launch + step;
     const int n = ctl->entries;
     const int per = (n + (int)gridDim.x - 1) / (int)gridDim.x;
     int e = (int)blockIdx.x * per;
@@ -836,23 +835,27 @@ __global__ __launch_bounds__(kBlockLO) void k_eval_batch(const BatchGraph* __res
         while (f < e_end && list[f].x == ent.x) ++f;
         int r1 = e;
         while (r1 < f && list[r1].z == 0) ++r1;
-        const BatchGraph& G = graphs[ent.x];
-        if (!G.skip) {  // not admitted yet, or finished
-            const EvalArgs& a = G.a;
+        // (uniform, so that the graph's arguments are scalar loads)
+        const BatchGraph& G = graphs[__builtin_amdgcn_readfirstlane(ent.x)];
+        const long long it = launch - G.first, last = G.max_iters;
+        if (it >= 0 && it <= last) {  // admitted and not finished
+            const EvalArgs a = batch_args(G, it);
             // the block holding the graph's first tile closes its previous iteration
+            // (requesting the first tile's constants ahead of the counters took 24 more
+            // registers and no time off)
             const float* m_sel = iteration_prologue(a, s_red, ent.z == 0 && ent.y == 0);
             if (m_sel) {
                 const float* __restrict__ m_in = uniform_ptr(m_sel);
                 float rmax = 0.0f;
                 unsigned int act = 0, sa = 0, sb = 0;
-                const int mode = G.mode_now;
+                const int mode = it == last ? kModeEvalOnly : G.mode;
                 if (mode == kModeLBP)
                     batch_run<kModeLBP>(a, m_in, list, e, r1 - e, f, l, s_part, rmax, act, sa, sb);
                 else if (mode == kModeRnBP)
                     batch_run<kModeRnBP>(a, m_in, list, e, r1 - e, f, l, s_part, rmax, act, sa, sb);
                 else
-                    batch_run<kModeEvalOnly>(a, m_in, list, e, r1 - e, f, l, s_part, rmax, act, sa,
-                                             sb);
+                    batch_run<kModeEvalOnly>(a, m_in, list, e, r1 - e, f, l, s_part, rmax, act,
+                                             sa, sb);
                 block_accumulate(&red, a.ctr, a.t, rmax, act, sa, sb);
             }
         }
@@ -4201,51 +4204,48 @@ int logodds_blocks_per_cu(int mode) {
     return e == hipSuccess ? n : 0;
 }
 
-// The done flag of every graph of a batch, gathered for one readback.
-__global__ void k_batch_status(const BatchGraph* graphs, int num_graphs, unsigned int* done) {
+// After a step: the done flag of every graph, gathered for one readback, and the
+// launch counter advanced by the step's launches.
+__global__ void k_batch_status(const BatchGraph* graphs, int num_graphs, unsigned int* done,
+                               BatchCtl* ctl, int launches) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g == 0) ctl->launch += launches;
     if (g >= num_graphs) return;
     const DevState* st = graphs[g].a.st;
     done[g] = st ? st->done : 0u;
 }
 
 hipError_t launch_batch_status(const BatchGraph* graphs, int num_graphs, unsigned int* done,
-                               hipStream_t s) {
-    k_batch_status<<<(num_graphs + 255) / 256, 256, 0, s>>>(graphs, num_graphs, done);
+                               BatchCtl* ctl, int launches, hipStream_t s) {
+    k_batch_status<<<(num_graphs + 255) / 256, 256, 0, s>>>(graphs, num_graphs, done, ctl, launches);
     return hipGetLastError();
 }
 
-hipError_t launch_eval_batch(BatchGraph* graphs, int num_graphs, const int* list, BatchCtl* ctl,
-                             int grid, hipStream_t s) {
-    k_batch_advance<<<(num_graphs + 255) / 256, 256, 0, s>>>(graphs, num_graphs, ctl);
-    k_eval_batch<<<grid, kBlockLO, 0, s>>>(graphs, (const int4*)list, ctl);
+hipError_t launch_eval_batch(const BatchGraph* graphs, const int* list, const BatchCtl* ctl,
+                             int step, int grid, hipStream_t s) {
+    k_eval_batch<<<grid, kBlockLO, 0, s>>>(graphs, (const int4*)list, ctl, step);
     return hipGetLastError();
 }
 
-hipError_t batch_graph_nodes(BatchGraph* graphs, int num_graphs, const int* list, BatchCtl* ctl,
+hipError_t batch_graph_nodes(const BatchGraph* graphs, const int* list, const BatchCtl* ctl,
                              int grid, int launches, hipGraph_t* out) {
     hipGraph_t gr = nullptr;
     hipError_t e = hipGraphCreate(&gr, 0);
     if (e != hipSuccess) return e;
-    void* adv_args[3] = {(void*)&graphs, (void*)&num_graphs, (void*)&ctl};
     const int4* lst = (const int4*)list;
-    void* ev_args[3] = {(void*)&graphs, (void*)&lst, (void*)&ctl};
-    hipKernelNodeParams pa{};
-    pa.func = (void*)k_batch_advance;
-    pa.gridDim = dim3((unsigned)((num_graphs + 255) / 256));
-    pa.blockDim = dim3(256);
-    pa.kernelParams = adv_args;
-    hipKernelNodeParams pe{};
-    pe.func = (void*)k_eval_batch;
-    pe.gridDim = dim3((unsigned)grid);
-    pe.blockDim = dim3(kBlock);
-    pe.kernelParams = ev_args;
+    int step = 0;
+    void* args[4] = {(void*)&graphs, (void*)&lst, (void*)&ctl, (void*)&step};
+    hipKernelNodeParams p{};
+    p.func = (void*)k_eval_batch;
+    p.gridDim = dim3((unsigned)grid);
+    p.blockDim = dim3(kBlockLO);
+    p.kernelParams = args;
     hipGraphNode_t prev = nullptr;
-    for (int k = 0; k < launches && e == hipSuccess; ++k) {
-        hipGraphNode_t na = nullptr, ne = nullptr;
-        e = hipGraphAddKernelNode(&na, gr, prev ? &prev : nullptr, prev ? 1 : 0, &pa);
-        if (e == hipSuccess) e = hipGraphAddKernelNode(&ne, gr, &na, 1, &pe);
-        prev = ne;
+    // (adding a node copies its arguments)
+    for (; step < launches && e == hipSuccess; ++step) {
+        hipGraphNode_t node = nullptr;
+        e = hipGraphAddKernelNode(&node, gr, prev ? &prev : nullptr, prev ? 1 : 0, &p);
+        prev = node;
     }
     if (e != hipSuccess) {
         (void)hipGraphDestroy(gr);

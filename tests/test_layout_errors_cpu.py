@@ -2,12 +2,13 @@
 import numpy as np
 import pytest
 
-from paper_1909_11469_amd import bp, inputs
+from paper_1909_11469_amd import inputs
 
 N = 40
 
 
 def _message(edges):
+    from paper_1909_11469_amd import bp  # (not at collection: GPU tests load torch first)
     edges = np.array(edges, dtype=np.int32)
     prob = dict(N=N, K=2, edges=edges, log_unary=np.zeros((N, 2)), pair_kind=inputs.PAIR_ISING,
                 coupling=np.full(len(edges), 0.5))
