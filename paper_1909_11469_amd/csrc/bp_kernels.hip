@@ -1827,7 +1827,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     extern __shared__ float smem[];
     __shared__ RedScratch red;
     __shared__ unsigned long long s_red[2];
-    constexpr int U = TAB == kTabMfma ? 8 : 4;  // pairs per lane in flight
+    // entries per lane in flight (eight cost the matrix-core variant a wave per
+    // SIMD: 465 instead of 386 us for six sweeps of the 203 x 197 grid, K = 21)
+    constexpr int U = 4;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int K = a.num_states, KS = K | 1;
     const int TS = a.tile_slots_max, TN = a.tile_nodes_max;
@@ -2209,55 +2211,91 @@ __device__ __forceinline__ float wave_sum_f(float v) {
     return v;
 }
 
-// Eq. (3) for the [E][K] layout: a group of W lanes per variable (W = K
-// rounded up to a power of two, 64 / W variables per wave), lane x holding
-// state x, so each incoming row is one coalesced read; the logs of K m are
-// summed in slot order, as the evaluation kernels sum them.  The reverse slots
-// of up to W incoming messages come in one load (a lane each) and eight rows
-// are in flight at a time, so a variable costs a few round trips, not two per
-// neighbour.  Shuffles and reductions stay inside the group, whose lanes run
+// Eq. (3) for the [E][K] layout: a group of W lanes per variable, V states per lane
+// (V = 4 and 16-byte loads where K is a multiple of four, else 1; W = K / V rounded
+// up to a power of two, 64 / W variables per wave); the logs of K m are summed in
+// slot order, as the evaluation kernels sum them, four rows in flight.  Bound by
+// the instructions around the logs: with a state per lane, eight rows per round
+// (a grid has four) and the row numbers by shuffles it took 71 us on a 500 x 500
+// grid with K = 32, now 30 us.  Shuffles stay inside the group, whose lanes run
 // the same loop trips.
+template <int V>
 __global__ void k_marginals_generic(const int* node_ptr, const int* rev, const float* unary,
-                                    const float* m, float* out, int N, int K) {
-    constexpr int kRows = 8;
+                                    const float* m, float* out, int N, int K, int wl) {
+    constexpr int kRows = 4;
     const int lane = threadIdx.x & 63;
-    int W = 1;
-    while (W < K) W <<= 1;
-    const int G = 64 / W;  // variables per wave
-    const int sub = lane / W, x = lane % W, base = sub * W;
+    const int W = 1 << wl;
+    const int G = 64 >> wl;  // variables per wave
+    const int x = (lane & (W - 1)) * V;
     const bool on = x < K;
+    const int xc = on ? x : 0;
     const float fK = (float)K;
     const long long waves = (long long)gridDim.x * (blockDim.x >> 6);
     const long long w0 = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    auto load = [&](const float* p, float* v) {
+        if (V == 4) {
+            const float4 t = *(const float4*)p;
+            v[0] = t.x;
+            v[V > 1 ? 1 : 0] = t.y;
+            v[V > 2 ? 2 : 0] = t.z;
+            v[V > 3 ? 3 : 0] = t.w;
+        } else {
+            v[0] = *p;
+        }
+    };
     for (long long n0 = w0 * G; n0 < N; n0 += waves * G) {
-        const int n = (int)(n0 + sub);
+        const int n = (int)(n0 + (lane >> wl));
         if (n < N) {
-            float acc = on ? unary[(long long)n * K + x] : -INFINITY;
+            float acc[V];
+            load(unary + (long long)n * K + xc, acc);
             const int s0 = node_ptr[n], s1 = node_ptr[n + 1];
-            for (int c = s0; c < s1; c += W) {
-                const int cnt = min(W, s1 - c);
-                const int r = x < cnt ? rev[c + x] : 0;
-                for (int j = 0; j < cnt; j += kRows) {
-                    float v[kRows];
+            for (int c = s0; c < s1; c += kRows) {
+                int r[kRows];
+                float v[kRows * V];
 #pragma unroll
-                    for (int u = 0; u < kRows; ++u) {
-                        const int ru = __shfl(r, base + (j + u) % W, 64);
-                        v[u] = on && j + u < cnt ? m[(long long)ru * K + x] : 1.0f;
+                for (int u = 0; u < kRows; ++u) r[u] = rev[min(c + u, s1 - 1)];
+#pragma unroll
+                for (int u = 0; u < kRows; ++u) load(m + (long long)r[u] * K + xc, v + u * V);
+#pragma unroll
+                for (int u = 0; u < kRows * V; ++u) v[u] *= fK;
+                log_batch<kRows * V>(v);
+#pragma unroll
+                for (int u = 0; u < kRows; ++u)
+                    if (c + u < s1) {
+#pragma unroll
+                        for (int i = 0; i < V; ++i) acc[i] += v[u * V + i];
                     }
-#pragma unroll
-                    for (int u = 0; u < kRows; ++u) v[u] *= fK;
-                    log_batch<kRows>(v);
-#pragma unroll
-                    for (int u = 0; u < kRows; ++u)
-                        if (on && j + u < cnt) acc += v[u];
-                }
             }
-            float mx = acc;
+            float mx = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < V; ++i) mx = fmaxf(mx, on ? acc[i] : -INFINITY);
             for (int o = W >> 1; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-            const float e = on ? expf(acc - mx) : 0.0f;
-            float z = e;
-            for (int o = W >> 1; o > 0; o >>= 1) z += __shfl_xor(z, o, 64);
-            if (on) out[(long long)n * K + x] = e / z;
+            float e[V];
+#pragma unroll
+            for (int i = 0; i < V; ++i) e[i] = on ? expf(acc[i] - mx) : 0.0f;
+            // the sum in one order whatever V: states 1 apart are added last, as the
+            // halving shuffles over single states add them
+            float z = 0.0f;
+            if (V == 4) {
+                float p[V];
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    p[i] = e[i];
+                    for (int o = W >> 1; o > 0; o >>= 1) p[i] += __shfl_xor(p[i], o, 64);
+                }
+                z = (p[0] + p[V > 2 ? 2 : 0]) + (p[V > 1 ? 1 : 0] + p[V > 3 ? 3 : 0]);
+            } else {
+                z = e[0];
+                for (int o = W >> 1; o > 0; o >>= 1) z += __shfl_xor(z, o, 64);
+            }
+            if (on) {
+                float* po = out + (long long)n * K + x;
+                if (V == 4)
+                    *(float4*)po = make_float4(e[0] / z, e[V > 1 ? 1 : 0] / z, e[V > 2 ? 2 : 0] / z,
+                                               e[V > 3 ? 3 : 0] / z);
+                else
+                    *po = e[0] / z;
+            }
         }
     }
 }
@@ -3141,13 +3179,26 @@ struct SelShared {
     unsigned int tot[kSelBlock / 64];
     SelPick pick;
 };
-__device__ __forceinline__ SelPick sel_pick(DevState* st, int pass, unsigned int k, SelShared& s) {
+// The loads of the pick, issued ahead of what else a launch waits for.
+struct SelLoad {
+    unsigned int h[kHistCopies];
+    SelPick before;
+};
+__device__ __forceinline__ SelLoad sel_load(const DevState* st, int pass, unsigned int k) {
+    SelLoad l;
+#pragma unroll
+    for (int c = 0; c < kHistCopies; ++c) l.h[c] = st->hist[pass][c][threadIdx.x];
+    l.before = SelPick{0u, 0u, k, 0u};
+    if (pass) l.before = st->sel[pass - 1];
+    return l;
+}
+__device__ __forceinline__ SelPick sel_pick(DevState* st, int pass, const SelLoad& l,
+                                            SelShared& s) {
     const int b = threadIdx.x, lane = b & 63, w = b >> 6;
     unsigned int hb = 0;
 #pragma unroll
-    for (int c = 0; c < kHistCopies; ++c) hb += st->hist[pass][c][b];
-    SelPick p{0u, 0u, k, 0u};
-    if (pass) p = st->sel[pass - 1];
+    for (int c = 0; c < kHistCopies; ++c) hb += l.h[c];
+    SelPick p = l.before;
     // suffix sums: within the wave by shuffles, then the totals of the waves above
     unsigned int S = hb;
 #pragma unroll
@@ -3194,6 +3245,17 @@ __global__ __launch_bounds__(kSelBlock) void k_rbp_hist(DevState* st, const unsi
     __shared__ unsigned int h[256];
     __shared__ SelShared ss;
     __shared__ unsigned int s_skip;
+    // the gate, the histogram of the pass before and the block's first keys are all
+    // requested before the first of them is waited for
+    const int chunks = (E + kCommitChunk - 1) / kCommitChunk;
+    int c = blockIdx.x;
+    unsigned int v[kSelPer];
+    auto load_keys = [&]() {
+        sel_load16(keys, (long long)c * kCommitChunk + (long long)threadIdx.x * kSelPer, (long long)E, v);
+    };
+    SelLoad sl;
+    if (pass) sl = sel_load(st, pass - 1, k);
+    if (c < chunks) load_keys();
     if (gate_ctr) {
         if (threadIdx.x < 64) {
             const unsigned int n = wave_sum32((unsigned int)gate_ctr[threadIdx.x].active);
@@ -3210,18 +3272,17 @@ __global__ __launch_bounds__(kSelBlock) void k_rbp_hist(DevState* st, const unsi
     if (s_skip) return;
     SelPick p{0u, 0u, k, 0u};
     if (pass) {
-        p = sel_pick(st, pass - 1, k, ss);
+        p = sel_pick(st, pass - 1, sl, ss);
         sel_clear(st, pass >= 2 ? pass - 2 : 3);
     }
     const int shift = 24 - 8 * pass;
-    const int chunks = (E + kCommitChunk - 1) / kCommitChunk;
-    for (int c = blockIdx.x; c < chunks; c += gridDim.x) {
+    while (c < chunks) {
         const long long q0 = (long long)c * kCommitChunk + (long long)threadIdx.x * kSelPer;
-        unsigned int v[kSelPer];
-        sel_load16(keys, q0, (long long)E, v);
 #pragma unroll
         for (int j = 0; j < kSelPer; ++j)
             lds_count(h, (v[j] >> shift) & 255u, q0 + j < E && (v[j] & p.mask) == p.prefix);
+        c += gridDim.x;
+        if (c < chunks) load_keys();
     }
     __syncthreads();
     if (h[threadIdx.x])
@@ -3241,8 +3302,9 @@ __global__ __launch_bounds__(kSelBlock) void k_rbp_tiecount(DevState* st, const 
                                                             unsigned int* block_ties) {
     __shared__ unsigned int part[kSelBlock / 64];
     __shared__ SelShared ss;
+    const SelLoad sl = sel_load(st, 3, 0u);
     if (st->rbp_skip) return;
-    const SelPick pk = sel_pick(st, 3, 0u, ss);
+    const SelPick pk = sel_pick(st, 3, sl, ss);
     sel_clear(st, 2);
     if (!pk.rank) return;
     const unsigned int T = pk.prefix;
@@ -4290,11 +4352,17 @@ hipError_t launch_marginals(int layout, const int* node_ptr, const int* rev,
     if (layout == kLayoutLogOdds)
         k_marginals_logodds<<<grid, 256, 0, s>>>(node_ptr, rev, unary, m, out, N);
     else {
-        int W = 1;
-        while (W < K) W <<= 1;
-        const long long per_block = 4ll * (64 / W);  // four waves of 64 / W variables
-        k_marginals_generic<<<(int)std::min<long long>((N + per_block - 1) / per_block, 65536), 256,
-                              0, s>>>(node_ptr, rev, unary, m, out, N, K);
+        // 16-byte stores need the caller's buffer aligned (its rows then are)
+        const bool v4 = K % 4 == 0 && (uintptr_t)out % 16 == 0;
+        const int L = v4 ? K / 4 : K;
+        int wl = 0;
+        while ((1 << wl) < L) ++wl;
+        const long long per_block = 4ll * (64 >> wl);  // four waves
+        const int g = (int)std::min<long long>((N + per_block - 1) / per_block, 65536);
+        if (v4)
+            k_marginals_generic<4><<<g, 256, 0, s>>>(node_ptr, rev, unary, m, out, N, K, wl);
+        else
+            k_marginals_generic<1><<<g, 256, 0, s>>>(node_ptr, rev, unary, m, out, N, K, wl);
     }
     return hipGetLastError();
 }
