@@ -1223,7 +1223,6 @@ __device__ __forceinline__ void slot_update_mfma32(const EvalArgs& a, const Flag
         c[4 * t4 + 2] = c4.z;
         c[4 * t4 + 3] = c4.w;
     }
-    if (!valid) return;
     if (fr.on) {
         // the flag is the sign of the row's first entry (lane h = 0 holds it)
         if (fr.alt && __shfl((int)(__float_as_uint(old[0]) >> 31), m, 64)) {
@@ -1251,39 +1250,37 @@ __device__ __forceinline__ void slot_update_mfma32(const EvalArgs& a, const Flag
         r = fmaxf(r, fabsf(c[t] - old[t]));
     }
     r = fmaxf(r, __shfl_xor(r, 32, 64));
-    const bool active = r > a.eps;
+    const bool active = valid && r > a.eps;
     const bool lead = h == 0;  // counts once per slot
-    rmax = fmaxf(rmax, r);
+    if (valid) rmax = fmaxf(rmax, r);
     act += active && lead;
-    float4* o0 = (float4*)(a.out_buf[0] + eo);
+    if (MODE == kModeEvalOnly) return;
+    // What is stored whole goes back through the wave's LDS rows, so that eight lanes
+    // write the 128 bytes of a row in one request: from the lane pair's registers every
+    // store would be 16 bytes of 64 rows, four requests for each 64 bytes.
+    float* dst;
     if (MODE == kModeLBP) {
-#pragma unroll
-        for (int t4 = 0; t4 < 4; ++t4)
-            o0[t4] = make_float4(c[4 * t4], c[4 * t4 + 1], c[4 * t4 + 2], c[4 * t4 + 3]);
-    } else if (MODE == kModeRnBP) {
+        dst = a.out_buf[0];
+    } else if (MODE == kModeRBP) {
+        dst = a.cand;
+        if (lead && valid) a.keys[sl] = __float_as_uint(r);
+    } else {
         bool ka = false, kb = false;
         if (active) {
-            const int node = n0 + v;
-            const unsigned int u24 = draw24(a, node, q - s_ptr[v]);
+            const unsigned int u24 = draw24(a, n0 + v, q - s_ptr[v]);
             ka = u24 < a.thr_a;
             kb = u24 < a.thr_b;
         }
         sa += ka && lead;
         sb += kb && lead;
+        // the whole row of outcome p_out; with two outcomes (row_flags) its first
+        // entry's sign bit set where they differ, the other outcome's row only there
+        bool kp = ka;
+        dst = a.out_buf[0];
         if (a.row_flags) {
-            // the whole row of outcome p_out, its first entry's sign bit set where
-            // the outcomes differ; the other outcome's row only there
-            const bool kp = p_out == 0 ? ka : kb, ko = p_out == 0 ? kb : ka;
-            const bool diff = ka != kb;
-            float4* op = (float4*)(a.out_buf[p_out] + eo);
-#pragma unroll
-            for (int t4 = 0; t4 < 4; ++t4) {
-                float4 v = kp ? make_float4(c[4 * t4], c[4 * t4 + 1], c[4 * t4 + 2], c[4 * t4 + 3])
-                              : make_float4(old[4 * t4], old[4 * t4 + 1], old[4 * t4 + 2],
-                                            old[4 * t4 + 3]);
-                if (t4 == 0 && h == 0 && diff) v.x = __uint_as_float(__float_as_uint(v.x) | 0x80000000u);
-                op[t4] = v;
-            }
+            const bool ko = p_out == 0 ? kb : ka, diff = ka != kb;
+            kp = p_out == 0 ? ka : kb;
+            dst = a.out_buf[p_out];
             if (diff) {
                 float4* os = (float4*)(a.out_buf[p_out ^ 1] + eo);
 #pragma unroll
@@ -1292,25 +1289,23 @@ __device__ __forceinline__ void slot_update_mfma32(const EvalArgs& a, const Flag
                                 : make_float4(old[4 * t4], old[4 * t4 + 1], old[4 * t4 + 2],
                                               old[4 * t4 + 3]);
             }
-            return;
+#pragma unroll
+            for (int t = 0; t < 16; ++t) c[t] = kp ? c[t] : old[t];
+            if (h == 0) c[0] = flag_first(c[0], diff);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 16; ++t) c[t] = kp ? c[t] : old[t];
         }
+    }
 #pragma unroll
-        for (int t4 = 0; t4 < 4; ++t4)
-            o0[t4] = ka ? make_float4(c[4 * t4], c[4 * t4 + 1], c[4 * t4 + 2], c[4 * t4 + 3])
-                        : make_float4(old[4 * t4], old[4 * t4 + 1], old[4 * t4 + 2], old[4 * t4 + 3]);
-        if (a.two_outputs) {
-            float4* o1 = (float4*)(a.out_buf[1] + eo);
+    for (int t4 = 0; t4 < 4; ++t4)
+        *(float4*)(rows + m * KS + 16 * h + 4 * t4) =
+            make_float4(c[4 * t4], c[4 * t4 + 1], c[4 * t4 + 2], c[4 * t4 + 3]);
 #pragma unroll
-            for (int t4 = 0; t4 < 4; ++t4)
-                o1[t4] = kb ? make_float4(c[4 * t4], c[4 * t4 + 1], c[4 * t4 + 2], c[4 * t4 + 3])
-                            : make_float4(old[4 * t4], old[4 * t4 + 1], old[4 * t4 + 2], old[4 * t4 + 3]);
-        }
-    } else if (MODE == kModeRBP) {
-        float4* oc = (float4*)(a.cand + eo);
-#pragma unroll
-        for (int t4 = 0; t4 < 4; ++t4)
-            oc[t4] = make_float4(c[4 * t4], c[4 * t4 + 1], c[4 * t4 + 2], c[4 * t4 + 3]);
-        if (lead) a.keys[sl] = __float_as_uint(r);
+    for (int j = 0; j < 4; ++j) {
+        const int i = (lane >> 3) + 8 * j, x = 4 * (lane & 7);
+        const float4 v4 = *(const float4*)(rows + i * KS + x);
+        if (32 * w + i < ns) *(float4*)(dst + (long long)(s0 + 32 * w + i) * K + x) = v4;
     }
 }
 
