@@ -2936,15 +2936,19 @@ __device__ __forceinline__ void sparse_eval_chunk(const EvalArgs& a, float L, in
 __global__ __launch_bounds__(kBlock) void k_sparse_eval(EvalArgs a) {
     __shared__ int s_d[kBlock / 64];
     __shared__ unsigned int s_ev[kBlock / 64];
-    if (a.st->done) return;
+    // (the flag, the slot range and the unary are requested together, and the done
+    // flag with them: a node's chain is then three round trips, not five)
+    const unsigned int done = a.st->done;
     const float* __restrict__ m = a.in_buf[0];
     int delta = 0;
     unsigned int ev = 0;
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < a.num_nodes; i += sparse_grid_stride()) {
-        if (!a.dirty[i]) continue;
-        a.dirty[i] = 0;
+        const unsigned char dirty = a.dirty[i];
         const int s0 = a.node_ptr[i], s1 = a.node_ptr[i + 1];
         const float u = a.unary[i];
+        __builtin_amdgcn_sched_barrier(0);
+        if (done || !dirty) continue;
+        a.dirty[i] = 0;
         unsigned int act = 0, old_act = 0;
         if (s1 > s0) {
             SparseChunk d;
@@ -2970,6 +2974,7 @@ __global__ __launch_bounds__(kBlock) void k_sparse_eval(EvalArgs a) {
         delta += (int)act - (int)old_act;
         ev += (unsigned int)(s1 - s0);
     }
+    if (done) return;
     sparse_accumulate(a.ctr, a.t, delta, ev, s_d, s_ev, false);
 }
 
@@ -2986,13 +2991,15 @@ __global__ __launch_bounds__(kBlock) void k_sparse_commit(EvalArgs a) {
     __shared__ unsigned long long s_n[3];
     __shared__ int s_d[kBlock / 64];
     __shared__ unsigned int s_ev[kBlock / 64];
+    // (the node's flag and slot range are requested together)
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    const bool mine = i < a.num_nodes && a.hasact[i];
-    int s0 = 0, s1 = 0;
+    const int ic = min(i, max(a.num_nodes - 1, 0));
+    const unsigned char flag = a.hasact[ic];
+    int s0 = a.node_ptr[ic], s1 = a.node_ptr[ic + 1];
+    __builtin_amdgcn_sched_barrier(0);
+    const bool mine = i < a.num_nodes && flag;
     unsigned int key[kSparseChunk] = {0u, 0u, 0u, 0u};
     if (mine) {
-        s0 = a.node_ptr[i];
-        s1 = a.node_ptr[i + 1];
 #pragma unroll
         for (int k = 0; k < kSparseChunk; ++k) key[k] = a.keys[min(s0 + k, s1 - 1)];
     }
