@@ -154,8 +154,9 @@ typedef struct bp_graph_desc {
 
 typedef struct bp_run_opts {
     int64_t max_iters;        /* maximum number of commits (sweeps); default 10000 */
-    int32_t check_every;      /* host polls the device convergence flag every this
-                                 many iterations; default 16; results do not depend on it */
+    int32_t check_every;      /* where the host polls the device state (profiling, launch-shape
+                                 tuning, the switch to sparse re-evaluation) it does so every
+                                 this many iterations; default 16; results do not depend on it */
     int32_t dynamic_p;        /* BP_RNBP: 1 = EdgeRatio rule (default), 0 = p_t = p */
     double high_p;            /* BP_RNBP dynamic: high setting, default 1.0 */
     double ratio_threshold;   /* BP_RNBP dynamic: default 0.9 */

@@ -876,18 +876,24 @@ static hipError_t run_events(bp_graph* g) {
     return e;
 }
 
-// Waits until `closed` evaluations of the run are closed or it has converged;
-// returns whether it has.  The stream is asked now and then, so that a failed
-// launch (whose error the next call returns) cannot keep the host here.
-static bool wait_progress(const bp_graph* g, hipStream_t s, unsigned long long closed) {
+// Waits until `closed` evaluations of the run are closed or it has converged, and
+// tells which.  The stream is asked now and then, so that neither a failed launch nor
+// a stream that cannot run (one under capture) can keep the host here.
+static hipError_t wait_progress(const bp_graph* g, hipStream_t s, unsigned long long closed,
+                                bool& converged) {
     for (unsigned int spins = 1;; ++spins) {
         const unsigned long long v = __atomic_load_n(g->prog, __ATOMIC_ACQUIRE);
-        if (v & 1) return true;
-        if ((v >> 1) >= closed) return false;
+        converged = (v & 1) != 0;
+        if (converged || (v >> 1) >= closed) return hipSuccess;
         if (spins % 64 == 0) {
-            if (spins % 16384 == 0 && hipStreamQuery(s) != hipErrorNotReady) {
-                // nothing is running any more: what was reported is final
-                return (__atomic_load_n(g->prog, __ATOMIC_ACQUIRE) & 1) != 0;
+            if (spins % 16384 == 0) {
+                const hipError_t e = hipStreamQuery(s);
+                if (e != hipErrorNotReady) {
+                    // nothing is running any more: what was reported is final
+                    converged = (__atomic_load_n(g->prog, __ATOMIC_ACQUIRE) & 1) != 0;
+                    return e;
+                }
+                (void)hipGetLastError();  // still running is no error of a later launch
             }
             sched_yield();
         }
@@ -1177,9 +1183,14 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
         // iteration: profiling, launch-shape tuning, the switch to sparse
         // re-evaluation.
         const bool follow = !prof_every && !tune && (o.sparse != 2 || sparse_now);
-        if (follow && it > kAhead && wait_progress(g, s, (unsigned long long)(it - kAhead))) {
-            --it;  // converged: nothing more to launch
-            break;
+        if (follow && it > kAhead) {
+            bool converged = false;
+            HIP_OK(wait_progress(g, s, (unsigned long long)(it - kAhead), converged),
+                   "follow the run");
+            if (converged) {
+                --it;  // nothing more to launch
+                break;
+            }
         }
         const long long t = t_start + it;
         final_launched = it == o.max_iters;
