@@ -1145,7 +1145,8 @@ __device__ __forceinline__ void mfma32_table(const EvalArgs& a, float* pb) {
 // 16-byte words.
 constexpr int kMfmaStride = 36;  // floats per row: 16-byte aligned, 8 rows span the 32 banks
 
-// p_out (row_flags): the outcome whose rows are written whole.
+// p_out (row_flags): the outcome whose rows are written whole.  ns >= 1: a lane past the
+// tile's slots reads the last one's row.
 template <int MODE, bool BF16 = false>
 __device__ __forceinline__ void slot_update_mfma32(const EvalArgs& a, const FlagRows& fr,
                                                    float* s_logm, const float* s_A,
@@ -1488,11 +1489,12 @@ __global__ __launch_bounds__(kBlock) void k_eval_mfma32(
     const int n0 = has ? a.tile_start[tile] : 0, n1 = has ? a.tile_start[tile + 1] : 0;
     const int s0 = has ? a.tile_slot[tile] : 0, s1 = has ? a.tile_slot[tile + 1] : 0;
     const int nn = n1 - n0, ns = s1 - s0;
-    // (a tile without slots reads row 0 and uses nothing of it)
-    if (tid < max(ns, 1)) l.rev[tid] = ns > 0 ? a.rev[s0 + tid] : 0;
+    if (tid < ns) l.rev[tid] = a.rev[s0 + tid];
     if (tid <= nn && has) l.ptr[tid] = a.node_ptr[n0 + tid] - s0;
     const float* m_sel = prologue_finish(a, cl, s_red, blockIdx.x == 0);
-    if (!m_sel || !has) return;
+    // (a tile without slots has no message to write and no row that its lanes could
+    // read in place of one: the buffers may start behind it, or hold nothing)
+    if (!m_sel || ns == 0) return;
     int p_out;
     const FlagRows fr = flag_inputs(a, m_sel, p_out);
     const float* __restrict__ m_in = fr.p;
@@ -1504,12 +1506,12 @@ __global__ __launch_bounds__(kBlock) void k_eval_mfma32(
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int i = tid + u * kBlock, q = i >> 3;
-        g4[u] = *(const float4*)(m_in + (long long)l.rev[min(q, max(ns - 1, 0))] * K +
+        g4[u] = *(const float4*)(m_in + (long long)l.rev[min(q, ns - 1)] * K +
                                  4 * (i & 7));
     }
     // unaries of node v (this thread's four positions p4 ..)
     auto load_unary = [&](int v, int p4) {
-        const float* un = a.unary + (long long)(n0 + min(v, max(nn - 1, 0))) * K;
+        const float* un = a.unary + (long long)(n0 + min(v, nn - 1)) * K;
         const int h = p4 >> 4, st = p4 & 15;
         return make_float4(un[mfma32_state<BF16>(st, h)], un[mfma32_state<BF16>(st + 1, h)],
                            un[mfma32_state<BF16>(st + 2, h)], un[mfma32_state<BF16>(st + 3, h)]);
