@@ -382,7 +382,10 @@ int bp_server_submit(bp_server* s, const bp_graph_desc* graph, const bp_request*
 /* Admit queued requests that fit, run `launches` batched iterations, then
  * retire the graphs that converged or reached max_iters (their results become
  * available to bp_server_result).  *finished (may be NULL) receives the number
- * retired by this call.  Synchronises the server's stream. */
+ * retired by this call.  Synchronises the server's stream.
+ * An error after the first of the step's launches ends the server: how far the
+ * resident graphs got is not known, so every later step returns that error.
+ * Results of requests retired before remain available. */
 int bp_server_step(bp_server* s, int32_t launches, int32_t* finished);
 
 /* Result of a retired request: Eq. (3) beliefs into host [N][2] FP32 and the
@@ -415,6 +418,10 @@ void bp_server_destroy(bp_server* s);
  * admissions fail as a device error during graph creation would (the request
  * is retired with BP_EDEVICE, its arena room returned).  0 turns it off. */
 int bp_server_inject_failures(bp_server* s, int32_t admissions);
+
+/* Test hook for the failure path of a step: the next step that launches fails as
+ * a device error right after its batched launches would. */
+int bp_server_inject_step_failure(bp_server* s);
 
 #ifdef __cplusplus
 }

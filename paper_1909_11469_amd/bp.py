@@ -36,7 +36,7 @@ EXPORTED = ["bp_default_opts", "bp_workspace_bytes", "bp_create_graph", "bp_run"
             "bp_graph_info_get", "bp_destroy_graph", "bp_last_error",
             "bp_server_create", "bp_server_submit", "bp_server_step", "bp_server_result",
             "bp_server_counts", "bp_server_config", "bp_server_destroy",
-            "bp_server_inject_failures"]
+            "bp_server_inject_failures", "bp_server_inject_step_failure"]
 
 
 class BpError(RuntimeError):
@@ -149,6 +149,8 @@ def _load():
     lib.bp_server_config.restype = ctypes.c_int
     lib.bp_server_inject_failures.argtypes = [P, ctypes.c_int32]
     lib.bp_server_inject_failures.restype = ctypes.c_int
+    lib.bp_server_inject_step_failure.argtypes = [P]
+    lib.bp_server_inject_step_failure.restype = ctypes.c_int
     return lib
 
 
@@ -457,6 +459,10 @@ class Server:
     def inject_failures(self, admissions):
         """Test hook: the next `admissions` admissions fail (bp_server_inject_failures)."""
         _check(lib.bp_server_inject_failures(self.handle, int(admissions)))
+
+    def inject_step_failure(self):
+        """Test hook: the next launching step fails (bp_server_inject_step_failure)."""
+        _check(lib.bp_server_inject_step_failure(self.handle))
 
     def counts(self):
         q, a, d = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int64()

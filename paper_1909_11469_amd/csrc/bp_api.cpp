@@ -1642,6 +1642,9 @@ struct bp_server {
     uint64_t done_off = 0;                 // unsigned [max_graphs]: gathered done flags
     unsigned int* h_done = nullptr;        // pinned mirror
     int inject_failures = 0;               // admissions still to fail (test hook)
+    int inject_step_failure = 0;           // the next launching step fails (test hook)
+    int failed = BP_OK;                    // the device error that ended the server
+    std::string failed_msg;
     uint64_t ctl_off = 0;                  // BatchCtl: launch counter, list length
     uint32_t options = 0;                  // BP_SERVER_*
     int num_cus = 1;
@@ -1908,11 +1911,11 @@ int bp_server_submit(bp_server* s, const bp_graph_desc* graph, const bp_request*
     return BP_OK;
 }
 
-int bp_server_step(bp_server* s, int32_t launches, int32_t* finished) {
-    if (finished) *finished = 0;
-    if (!s) return fail(BP_EINVAL, "server is NULL");
-    if (launches < 0) return fail(BP_EINVAL, "launches < 0");
-    DeviceGuard dg(s->device);
+}  // extern "C"
+
+// bp_server_step; started is set once device work that moves the resident graphs may
+// have been enqueued.
+static int server_step(bp_server* s, int32_t launches, int32_t* finished, bool& started) {
     int rc = server_admit(s);
     if (rc != BP_OK) return rc;
     rc = server_upload_list(s);
@@ -1928,7 +1931,8 @@ int bp_server_step(bp_server* s, int32_t launches, int32_t* finished) {
         s->tune_next = 0;
     const int tuning = tune ? s->tune_next : -1;
     const int grid = tuning >= 0 ? s->cand[tuning] : s->grid;
-    if (blocks > 0 && launches > 0) {
+    const bool launching = blocks > 0 && launches > 0;
+    if (launching) {
         if (tuning >= 0) HIP_OK(hipEventRecord(s->ev0, s->stream), "event record");
         if (s->options & BP_SERVER_GRAPHS) {
             if (!s->gexec || s->g_launches != launches || s->g_grid != grid ||
@@ -1948,24 +1952,30 @@ int bp_server_step(bp_server* s, int32_t launches, int32_t* finished) {
                 s->g_grid = grid;
                 s->g_list_off = s->list_off;
             }
+            started = true;
             HIP_OK(hipGraphLaunch(s->gexec, s->stream), "replay batched launches");
         } else {
+            started = true;
             for (int k = 0; k < launches; ++k)
                 HIP_OK(launch_eval_batch(graphs, list, ctl, k, grid, s->stream),
                        "batch evaluation");
         }
         if (tuning >= 0) HIP_OK(hipEventRecord(s->ev1, s->stream), "event record");
-        // the device counter advanced once per launch; with nothing resident
-        // neither moves
-        s->launch += launches;
+        if (s->inject_step_failure) {
+            s->inject_step_failure = 0;
+            return fail(BP_EDEVICE, "batched launches: injected failure");
+        }
     }
     // poll every resident graph (one gathered readback of the done flags),
     // retire the finished ones
     int n = 0;
     unsigned int* d_done = (unsigned int*)(s->base + s->done_off);
-    HIP_OK(launch_batch_status(graphs, s->max_graphs, d_done, ctl,
-                               blocks > 0 && launches > 0 ? launches : 0, s->stream),
+    started = true;
+    HIP_OK(launch_batch_status(graphs, s->max_graphs, d_done, ctl, launching ? launches : 0,
+                               s->stream),
            "batch status");
+    // the status kernel advances the device's launch counter by the same number
+    if (launching) s->launch += launches;
     HIP_OK(hipMemcpyAsync(s->h_done, d_done, sizeof(unsigned int) * (size_t)s->max_graphs,
                           hipMemcpyDeviceToHost, s->stream),
            "status readback");
@@ -2010,6 +2020,26 @@ int bp_server_step(bp_server* s, int32_t launches, int32_t* finished) {
     return BP_OK;
 }
 
+extern "C" {
+
+int bp_server_step(bp_server* s, int32_t launches, int32_t* finished) {
+    if (finished) *finished = 0;
+    if (!s) return fail(BP_EINVAL, "server is NULL");
+    if (launches < 0) return fail(BP_EINVAL, "launches < 0");
+    // after an error among a step's launches the two launch counters may disagree and
+    // iterations would be run twice: the resident graphs are not taken further
+    if (s->failed != BP_OK)
+        return fail(s->failed, "the server ended with an earlier error: %s", s->failed_msg.c_str());
+    DeviceGuard dg(s->device);
+    bool started = false;
+    const int rc = server_step(s, launches, finished, started);
+    if (rc != BP_OK && started) {
+        s->failed = rc;
+        s->failed_msg = g_last_error;
+    }
+    return rc;
+}
+
 int bp_server_result(bp_server* s, int64_t id, float* marginals, bp_run_stats* stats) {
     if (!s) return fail(BP_EINVAL, "server is NULL");
     auto it = s->reqs.find(id);
@@ -2048,6 +2078,12 @@ int bp_server_inject_failures(bp_server* s, int32_t admissions) {
     if (!s) return fail(BP_EINVAL, "server is NULL");
     if (admissions < 0) return fail(BP_EINVAL, "admissions < 0");
     s->inject_failures = admissions;
+    return BP_OK;
+}
+
+int bp_server_inject_step_failure(bp_server* s) {
+    if (!s) return fail(BP_EINVAL, "server is NULL");
+    s->inject_step_failure = 1;
     return BP_OK;
 }
 
