@@ -365,7 +365,7 @@ int build_layout(const bp_graph_desc* d, HostLayout& L) {
                 const int s0 = L.node_ptr[i], s1 = L.node_ptr[i + 1];
                 const int rec[8] = {s0,         s1 - s0, L.kv[i], L.uoff[i], L.moff[s0],
                                     L.moff[s1] - L.moff[s0], i,
-                                    (1 << 20) / L.kv[i] + 1};
+                                    (int)quotient_magic(L.kv[i])};
                 L.vrec.insert(L.vrec.end(), rec, rec + 8);
                 if ((1ll << c) >= ragged_wide_work(N)) ++L.num_wide;
             }
@@ -831,7 +831,7 @@ static EvalArgs run_args(const bp_graph* g, int schedule, double eps, double p, 
     a.tile_slots_max = L.tile_slots_max;
     a.tile_big = L.tile_big;
     a.pairs_route = L.pairs_route;
-    a.k_magic = (1u << 20) / (unsigned int)L.K + 1u;
+    a.k_magic = quotient_magic(L.K);
     for (a.k_wlog = 0; (1 << a.k_wlog) < L.K; ++a.k_wlog) {
     }
     a.no_mfma = L.no_mfma;

@@ -71,6 +71,25 @@ __host__ __device__ inline bool ragged_flat(int deg, int ki, int p) {
            p * ki <= kRaggedHeavyWork;
 }
 
+// Quotients by a state count without a division: i / K = (i * quotient_magic(K)) >> 20,
+// with a 32-bit product.  The multiplier is (2^20 + d) / K with 1 <= d <= K, so the
+// quotient is exact while i d < 2^20 and the product does not wrap: for every i
+// below `limit` and K from kmin to kmax if this holds.
+constexpr unsigned int quotient_magic(int K) { return (1u << 20) / (unsigned int)K + 1u; }
+constexpr bool quotient_exact(int kmin, int kmax, unsigned long long limit) {
+    for (int K = kmin; K <= kmax; ++K)
+        if ((limit - 1) * quotient_magic(K) > 0xFFFFFFFFull ||
+            (limit - 1) * (unsigned long long)K >= 1ull << 20)
+            return false;
+    return true;
+}
+// k_eval_pairs: the entries of a tile and what its last unrolled step runs past them
+// (K > 2: see pairs_route); the ragged kernel: the cavity entries of a variable.
+constexpr int kPairsUnroll = 4;
+static_assert(quotient_exact(3, kMaxK, kTileFloatsGeneric + kPairsUnroll * kBlock),
+              "tile entries past the exact quotients");
+static_assert(quotient_exact(2, kMaxKRagged, kRaggedFlat), "ragged entries past the exact quotients");
+
 // 0: one log-odds value per message (K = 2 Ising); 1: K floats per message;
 // 2: K_j floats per message i -> j (per-variable state counts)
 // The progress word is written every so many closed evaluations, and the host keeps
@@ -160,9 +179,8 @@ struct EvalArgs {
     const int* heavy;           // [num_heavy][2] {slot, source} of the slots of heavy variables
     int num_heavy;
     const int* vrec;            // [num_flat][8] {first slot, degree, K_i, first unary, first
-                                // message entry, message entries, variable, 2^20 / K_i + 1 (e / K_i
-                                // = e times it >> 20 for e < 8192)} of the variables
-                                // that are not heavy, by work
+                                // message entry, message entries, variable, quotient_magic(K_i)} of the
+                                // variables that are not heavy, by work
     int num_flat;
     int num_wide;               // the first records, each of which takes a block
     const int* rin;             // [E] first message entry of the reverse slot
@@ -198,7 +216,7 @@ struct EvalArgs {
     int tile_slots_max;         // [E][K] layout: most slots in one regular tile
     int tile_big;               // [E][K] layout: 1 if some node's slots exceed a tile
     int pairs_route;            // [E][K] layout: 1 if the graph takes k_eval_pairs
-    unsigned int k_magic;       // i / K = (i * k_magic) >> 20 for i < 16384
+    unsigned int k_magic;       // quotient_magic(K)
     int k_wlog;                 // log2 of K rounded up to a power of two
     int no_mfma;                // K = 32 shared table on the vector units (not the matrix cores)
     int mfma_bf16;              // K = 32 shared table: BF16 operands on the matrix cores

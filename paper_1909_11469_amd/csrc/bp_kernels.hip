@@ -1833,7 +1833,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     __shared__ unsigned long long s_red[2];
     // entries per lane in flight (eight cost the matrix-core variant a wave per
     // SIMD: 465 instead of 386 us for six sweeps of the 203 x 197 grid, K = 21)
-    constexpr int U = 4;
+    constexpr int U = kPairsUnroll;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int K = a.num_states, KS = K | 1;
     const int TS = a.tile_slots_max, TN = a.tile_nodes_max;
