@@ -135,7 +135,9 @@ Offsets plan(const HostLayout& L) {
     o.unary = a.take(sizeof(float) * L.unary.size());
     o.pair = a.take(sizeof(float) * L.pair_tab.size());
     o.orient = a.take(L.orient.size());
-    for (int i = 0; i < 4; ++i) o.msg[i] = a.take(sizeof(float) * (size_t)L.msg_floats);
+    // (one entry for a graph without edges: a K = 2 tile without slots reads slot 0)
+    for (int i = 0; i < 4; ++i)
+        o.msg[i] = a.take(sizeof(float) * (size_t)std::max(L.msg_floats, 1ll));
     o.cand = a.take(sizeof(float) * (size_t)L.msg_floats);
     o.keys = a.take(sizeof(unsigned int) * E);
     // per-block tie counts of a top-k over the messages or (residual splash) the variables
