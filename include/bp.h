@@ -322,6 +322,13 @@ void bp_destroy_graph(bp_graph* g);
 /* Description of the last error in the calling thread ("" if none). */
 const char* bp_last_error(void);
 
+/* Test hook: the kernels take log and exp in short forms where the arguments allow
+ * it, which must equal the device library's functions bit for bit.  Compares them
+ * on every float of the ranges (log: normal and positive; exp: -100 ... 0) on the
+ * current device; *log_diffs and *exp_diffs (either may be NULL) receive the number
+ * of floats that differ. */
+int bp_check_short_math(uint64_t* log_diffs, uint64_t* exp_diffs);
+
 /* ------------------------------------------------------------------------
  * Serving: many independent graphs solved together.
  *

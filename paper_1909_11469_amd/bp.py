@@ -33,7 +33,7 @@ SCHEDULES = {"lbp": BP_LBP, "rbp": BP_RBP, "rnbp": BP_RNBP, "rs": BP_RS}
 # Every symbol include/bp.h declares.
 EXPORTED = ["bp_default_opts", "bp_workspace_bytes", "bp_create_graph", "bp_run",
             "bp_run_noalloc", "bp_marginals", "bp_marginals_device", "bp_get_state", "bp_set_state",
-            "bp_graph_info_get", "bp_destroy_graph", "bp_last_error",
+            "bp_graph_info_get", "bp_destroy_graph", "bp_last_error", "bp_check_short_math",
             "bp_server_create", "bp_server_submit", "bp_server_step", "bp_server_result",
             "bp_server_counts", "bp_server_config", "bp_server_destroy",
             "bp_server_inject_failures", "bp_server_inject_step_failure"]
@@ -129,6 +129,8 @@ def _load():
     lib.bp_destroy_graph.restype = None
     lib.bp_last_error.argtypes = []
     lib.bp_last_error.restype = ctypes.c_char_p
+    lib.bp_check_short_math.argtypes = [ctypes.POINTER(ctypes.c_uint64)] * 2
+    lib.bp_check_short_math.restype = ctypes.c_int
     I64P = ctypes.POINTER(ctypes.c_int64)
     lib.bp_server_create.argtypes = [ctypes.POINTER(bp_server_desc), ctypes.POINTER(P)]
     lib.bp_server_create.restype = ctypes.c_int
@@ -165,6 +167,14 @@ def _check(rc):
     if rc < 0:
         raise BpError(rc, bp_last_error())
     return rc
+
+
+def bp_check_short_math():
+    """Test hook: (log, exp) floats on which the kernels' short forms differ from the
+    device library's functions (include/bp.h)."""
+    a, b = ctypes.c_uint64(), ctypes.c_uint64()
+    _check(lib.bp_check_short_math(ctypes.byref(a), ctypes.byref(b)))
+    return a.value, b.value
 
 
 def bp_default_opts():

@@ -601,6 +601,19 @@ void bp_default_opts(bp_run_opts* o) {
 
 const char* bp_last_error(void) { return g_last_error.c_str(); }
 
+int bp_check_short_math(uint64_t* log_diffs, uint64_t* exp_diffs) {
+    unsigned long long *dev = nullptr, host[2] = {0, 0};
+    HIP_OK(hipMalloc((void**)&dev, sizeof(host)), "hipMalloc");
+    hipError_t e = hipMemcpy(dev, host, sizeof(host), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = launch_check_short_math(dev, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(host, dev, sizeof(host), hipMemcpyDeviceToHost);
+    (void)hipFree(dev);
+    if (e != hipSuccess) return hip_fail(e, "comparison of log and exp");
+    if (log_diffs) *log_diffs = host[0];
+    if (exp_diffs) *exp_diffs = host[1];
+    return BP_OK;
+}
+
 int bp_workspace_bytes(const bp_graph_desc* desc, uint64_t* bytes) {
     HostLayout L;
     int rc = build_layout(desc, L);

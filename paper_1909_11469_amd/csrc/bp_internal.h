@@ -280,6 +280,7 @@ hipError_t batch_graph_nodes(const BatchGraph* graphs, const int* list, const Ba
 hipError_t launch_batch_status(const BatchGraph* graphs, int num_graphs, unsigned int* done,
                                BatchCtl* ctl, int launches, hipStream_t s);
 hipError_t launch_init_state(DevState* st, CounterLine* ctr, hipStream_t s);
+hipError_t launch_check_short_math(unsigned long long* diff, hipStream_t s);
 hipError_t launch_fill(float* p, float v, long long n, hipStream_t s);
 hipError_t launch_eval(int layout, int mode, const EvalArgs& a, hipStream_t s);
 // host: pinned memory that takes the first `bytes` of the state, or nullptr

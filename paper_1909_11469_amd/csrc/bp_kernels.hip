@@ -78,12 +78,19 @@ __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2
 __device__ __forceinline__ float log2_hw(float x) { return __builtin_amdgcn_logf(x); }
 __device__ __forceinline__ float rcp_hw(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// log x = ln 2 * log2 x for a normal finite x > 0, the factor as the sum of two
-// floats (the high one truncated), and exp x = 2^(x log2 e) for -100 <= x <= 0,
-// the product as the sum of two floats whose integer part goes to the exponent.
-// Bit for bit logf and expf on these ranges (compared over every float in them);
-// without the denormal, infinity and underflow handling that the library
-// functions add (6 and 4 of about 12 instructions).
+// Short forms of logf and expf, for a normal finite x > 0 and for -100 <= x <= 0: the
+// same bits without the denormal, infinity and underflow handling (6 and 4 of about
+// 12 instructions).  A wave takes the short form or the library's by a vote over its
+// lanes (log_batch, exp_batch), and other kernels call the library, so a result that
+// does not depend on its neighbours rests on the bits being equal:
+// bp_check_short_math compares every float of both ranges.
+//
+// The steps and the two-float constants are those of the LLVM AMDGPU backend's expansion
+// of llvm.log.f32 and llvm.exp.f32 (open source) with contraction.  log x = y ln 2 with
+// y = log2 x and ln 2 = hi + lo: e collects y lo and the rounding error of y hi; the
+// last step, contracted, multiplies again without rounding, so that error enters
+// twice (at most half an ulp).  exp x = 2^(x log2 e): the product as the sum p + q
+// of two floats, whose integer part goes to the exponent.
 __device__ __forceinline__ float log_normal(float x) {
 #pragma clang fp contract(off)
     constexpr float hi = 0x1.62e42ep-1f, lo = 0x1.efa39ep-25f;
@@ -126,6 +133,26 @@ __device__ __forceinline__ void exp_batch(float* v) {
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] = expf(v[i]);
     }
+}
+
+// The floats of each range whose short form differs from the library's: diff[0] log,
+// diff[1] exp.
+constexpr unsigned int kLogFirst = 0x00800000u, kLogLast = 0x7F7FFFFFu;  // normal, positive
+constexpr unsigned int kExpFirst = 0x80000000u, kExpLast = 0xC2C80000u;  // -0 ... -100
+__global__ __launch_bounds__(kBlock) void k_check_short_math(unsigned long long* diff) {
+    const unsigned int id = blockIdx.x * kBlock + threadIdx.x, stride = gridDim.x * kBlock;
+    unsigned int dl = 0, de = 0;
+    for (unsigned long long b = kLogFirst + (unsigned long long)id; b <= kLogLast; b += stride) {
+        const float x = __uint_as_float((unsigned int)b);
+        dl += __float_as_uint(log_normal(x)) != __float_as_uint(logf(x));
+    }
+    for (unsigned long long b = kExpFirst + (unsigned long long)id; b <= kExpLast; b += stride) {
+        const float x = __uint_as_float((unsigned int)b);
+        de += __float_as_uint(exp_reduced(x)) != __float_as_uint(expf(x));
+    }
+    if (id == 0) de += __float_as_uint(exp_reduced(0.0f)) != __float_as_uint(expf(0.0f));
+    if (dl) atomicAdd(&diff[0], (unsigned long long)dl);
+    if (de) atomicAdd(&diff[1], (unsigned long long)de);
 }
 
 constexpr float kLog2e = 1.4426950408889634f;
@@ -4115,6 +4142,11 @@ __global__ void k_fill_u32(unsigned int* p, unsigned int v, long long n) {
 // ---------------------------------------------------------------------------
 hipError_t launch_init_state(DevState* st, CounterLine* ctr, hipStream_t s) {
     k_init_state<<<1, 256, 0, s>>>(st, ctr);
+    return hipGetLastError();
+}
+
+hipError_t launch_check_short_math(unsigned long long* diff, hipStream_t s) {
+    k_check_short_math<<<4096, kBlock, 0, s>>>(diff);
     return hipGetLastError();
 }
 
