@@ -972,7 +972,8 @@ __device__ __forceinline__ float flag_entry(const FlagRows& f, long long row, in
 }
 
 // Where a launch writes: whole rows of outcome `prim`, the other outcome's
-// rows where the decisions differ.
+// rows where the decisions differ.  (In this layout two outcomes always come with
+// flags: a launch without them has one.)
 __device__ __forceinline__ float flag_first(float v, bool diff) {
     return diff ? __uint_as_float(__float_as_uint(v) | 0x80000000u) : v;
 }
@@ -1120,10 +1121,6 @@ __device__ __forceinline__ void slot_update_split(const EvalArgs& a, const FlagR
         }
 #pragma unroll
         for (int j = 0; j < KR; ++j) a.out_buf[0][eo + j] = ka ? c[j] : old[j];
-        if (a.two_outputs) {
-#pragma unroll
-            for (int j = 0; j < KR; ++j) a.out_buf[1][eo + j] = kb ? c[j] : old[j];
-        }
     } else if (MODE == kModeRBP) {
 #pragma unroll
         for (int j = 0; j < KR; ++j) a.cand[eo + j] = c[j];
@@ -1713,20 +1710,21 @@ void k_eval_generic(EvalArgs a) {
         float c[KP];
 #pragma unroll
         for (int y = 0; y < KP; ++y) c[y] = 0.0f;
-        if (a.pair_kind == kPairIsing) {
+        // (Ising and per-slot tables: K = 2 only; wider tables of their own take
+        // k_eval_pairs)
+        if (KP == 2 && a.pair_kind == kPairIsing) {
             // exp(J s_i s_k) scaled by exp(-|J|): one entry is 1, the other exp(-2|J|)
             const float J = a.coupling[s];
             const float ep = expf(J - fabsf(J)), em = expf(-J - fabsf(J));
             c[0] = ep * g[0] + em * g[1];
             c[1] = em * g[0] + ep * g[1];
-        } else if (a.pair_kind != kPairDense) {
+        } else if (KP > 2 || a.pair_kind != kPairDense) {
             const ConstF P4 = (ConstF)(uintptr_t)a.pair;
             if (a.pair_kind == kPairSharedAsym && a.orient[s])
                 matvec_uniform<KP, true>(P4, g, c);
             else
                 matvec_uniform<KP, false>(P4, g, c);
         } else {
-            // per-slot tables (K = 2 only; wider ones take k_eval_pairs)
             const float* P = a.pair + (long long)s * K * K;
 #pragma unroll
             for (int x = 0; x < K; ++x)
@@ -1776,10 +1774,6 @@ void k_eval_generic(EvalArgs a) {
             } else {
 #pragma unroll
                 for (int y = 0; y < KP; ++y) a.out_buf[0][eo + y] = ka ? c[y] : old[y];
-                if (a.two_outputs) {
-#pragma unroll
-                    for (int y = 0; y < KP; ++y) a.out_buf[1][eo + y] = kb ? c[y] : old[y];
-                }
             }
         } else if (MODE == kModeRBP) {
 #pragma unroll
@@ -2163,7 +2157,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
                             if (diff) a.out_buf[p_out ^ 1][e0 + i] = ko ? v : old[j];
                         } else {
                             a.out_buf[0][e0 + i] = ka ? v : old[j];
-                            if (a.two_outputs) a.out_buf[1][e0 + i] = kb ? v : old[j];
                         }
                     }
                 }
