@@ -171,9 +171,6 @@ bool positive_all(const double* p, size_t n) {
     return true;
 }
 
-// Validate the problem (Eq. (1): finite state sets, positive potentials) and
-// build the device layout: directed messages sorted by (source, target), the
-// reverse-slot index, per-slot parameters and node tiles.
 // The error of the first edge that is out of range, a self-loop, or equal to an
 // earlier one (build_layout has found that there is one).
 int report_bad_edge(const bp_graph_desc* d) {
@@ -191,6 +188,9 @@ int report_bad_edge(const bp_graph_desc* d) {
     return fail(BP_EINVAL, "invalid edges");
 }
 
+// Validate the problem (Eq. (1): finite state sets, positive potentials) and
+// build the device layout: directed messages sorted by (source, target), the
+// reverse-slot index, per-slot parameters and node tiles.
 int build_layout(const bp_graph_desc* d, HostLayout& L) {
     if (!d) return fail(BP_EINVAL, "desc is NULL");
     const long long N = d->num_vars, K = d->num_states, M = d->num_edges;

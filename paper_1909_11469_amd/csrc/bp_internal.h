@@ -90,13 +90,13 @@ static_assert(quotient_exact(3, kMaxK, kTileFloatsGeneric + kPairsUnroll * kBloc
               "tile entries past the exact quotients");
 static_assert(quotient_exact(2, kMaxKRagged, kRaggedFlat), "ragged entries past the exact quotients");
 
-// 0: one log-odds value per message (K = 2 Ising); 1: K floats per message;
-// 2: K_j floats per message i -> j (per-variable state counts)
 // The progress word is written every so many closed evaluations, and the host keeps
 // at most kAhead launches ahead of what it says.
 constexpr unsigned long long kReportEvery = 4;
 constexpr long long kAhead = 8;
 
+// 0: one log-odds value per message (K = 2 Ising); 1: K floats per message;
+// 2: K_j floats per message i -> j (per-variable state counts)
 enum Layout : int { kLayoutLogOdds = 0, kLayoutGeneric = 1, kLayoutRagged = 2 };
 enum PairDev : int { kPairIsing = 0, kPairShared = 1, kPairSharedAsym = 2, kPairDense = 3 };
 enum Mode : int { kModeLBP = 0, kModeRnBP = 1, kModeRBP = 2, kModeEvalOnly = 3 };

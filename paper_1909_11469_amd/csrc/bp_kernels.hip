@@ -2361,9 +2361,6 @@ __global__ void k_marginals_generic(const int* node_ptr, const int* rev, const f
 // its other lanes (a wave executes its LDS operations in order).
 __device__ __forceinline__ void wave_lds_sync() { __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// LDS per wave of the flat path: the cavity vectors of one variable's slots,
-// and its slots' outputs (entries), each at most kRaggedFlat floats.
-
 template <int MODE>
 __device__ __forceinline__ void ragged_commit(const EvalArgs& a, int q, float v, float old, bool ka,
                                               bool kb) {
