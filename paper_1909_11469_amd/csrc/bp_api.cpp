@@ -79,6 +79,7 @@ struct HostLayout {
     int no_mfma = 0;                  // BP_FLAG_NO_MATRIX_CORES
     int mfma_bf16 = 0;                // BP_FLAG_BF16_MATRIX_CORES
     int sparse_reserved = 0;          // BP_FLAG_SPARSE_BUFFERS on a log-odds graph
+    int served = 0;                   // a server's graph: LBP and RnBP full evaluations only
     int splash_reserved = 0;          // BP_FLAG_SPLASH_BUFFERS on a log-odds graph
     std::vector<int> tiles4;          // log-odds layout: regular tiles {n0, n1, s0, s1}
     std::vector<int> big4;            // log-odds layout: single-node tiles over the slot limit
@@ -121,6 +122,10 @@ size_t sparse_bytes(const HostLayout& L) {
     return 2 * nb + sizeof(int) * (size_t)L.E + 256;
 }
 
+// Device bytes of a graph's run state.  A served graph holds its head only: the
+// top-k, sparse and splash parts, 32 KiB, would be a seventh of a 32 x 32 grid's memory.
+size_t state_bytes(const HostLayout& L) { return L.served ? kStateReadback : sizeof(DevState); }
+
 Offsets plan(const HostLayout& L) {
     Arena a;
     Offsets o;
@@ -142,7 +147,7 @@ Offsets plan(const HostLayout& L) {
     o.keys = a.take(sizeof(unsigned int) * E);
     // per-block tie counts of a top-k over the messages or (residual splash) the variables
     o.ties = a.take(sizeof(unsigned int) * (std::max<size_t>(E, (size_t)L.N) / 4096 + 2));
-    o.state = a.take(sizeof(DevState));
+    o.state = a.take(state_bytes(L));
     o.ctr = a.take(sizeof(CounterLine) * 4 * kCounterCopies);
     o.marg = a.take(sizeof(float) * (size_t)L.belief_floats);
     o.kv = a.take(sizeof(int) * L.kv.size());
@@ -526,10 +531,6 @@ int build_layout(const bp_graph_desc* d, HostLayout& L) {
 
 }  // namespace
 
-// The leading fields of DevState the host reads after a run or at a poll
-// (everything before the selection histograms).
-constexpr size_t kStateReadback = offsetof(DevState, hist);
-
 // Sparse mode 2 switches to sparse re-evaluation once n_t <= E / kSparseSwitch.
 #ifndef BP_SPARSE_SWITCH
 #define BP_SPARSE_SWITCH 16
@@ -711,7 +712,7 @@ int create_graph_from_layout(HostLayout& layout, const bp_graph_desc* desc, bp_g
     e = L.layout == kLayoutRagged
             ? launch_fill_ragged(g->msg(0, 0), g->at<int>(g->off.moff), (int)L.E, s)
             : launch_fill(g->msg(0, 0), uni, L.msg_floats, s);
-    if (e == hipSuccess) e = launch_init_state(g->st(), g->ctr(), s);
+    if (e == hipSuccess) e = launch_init_state(g->st(), state_bytes(L), g->ctr(), s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return give_back(hip_fail(e, "initialise"));
     g->cur_pair = 0;
@@ -1094,7 +1095,7 @@ static int run_impl(bp_graph* g, int schedule, double eps, double p, uint64_t se
     a.st = rs.st;
     a.ctr = rs.ctr;
     if (small) return run_small(g, mode, a, o, stats, !rs.noalloc);
-    HIP_OK(launch_init_state(rs.st, rs.ctr, s), "init state");
+    HIP_OK(launch_init_state(rs.st, sizeof(DevState), rs.ctr, s), "init state");
     // frontier RBP on the K = 2 kernel: the evaluation also counts the top-k's
     // first radix digit (not for oversized nodes, the sparse phase, or k = E)
     a.hist0 = (mode == kModeRBP && !splash && L.layout == kLayoutLogOdds && a.num_big == 0 &&
@@ -1911,6 +1912,7 @@ int bp_server_submit(bp_server* s, const bp_graph_desc* graph, const bp_request*
     int rc = build_layout(graph, L);  // full validation
     if (rc != BP_OK) return rc;
     if (L.layout != kLayoutLogOdds) return fail(BP_EINVAL, "graph too large for the log-odds layout");
+    L.served = 1;
     const uint64_t need = plan(L).total;
     if (need + 256 > s->bytes) return fail(BP_ENOMEM, "graph needs %llu bytes, arena has %llu",
                                            (unsigned long long)need, (unsigned long long)s->bytes);

@@ -154,6 +154,9 @@ struct DevState {
     unsigned int rs_count[kSplashMaxDepth + 1];
     unsigned int pad3;
 };
+// The head of DevState, which every run uses and the host reads after a run or at a
+// poll: everything before the selection histograms.
+constexpr size_t kStateReadback = offsetof(DevState, hist);
 
 struct EvalArgs {
     const int* tile_start;      // [T+1] first node of each tile ([E][K] layout)
@@ -279,7 +282,8 @@ hipError_t batch_graph_nodes(const BatchGraph* graphs, const int* list, const Ba
 // After a step of `launches` iterations: done flags, launch counter.
 hipError_t launch_batch_status(const BatchGraph* graphs, int num_graphs, unsigned int* done,
                                BatchCtl* ctl, int launches, hipStream_t s);
-hipError_t launch_init_state(DevState* st, CounterLine* ctr, hipStream_t s);
+// bytes: how much of the state there is
+hipError_t launch_init_state(DevState* st, size_t bytes, CounterLine* ctr, hipStream_t s);
 hipError_t launch_check_short_math(unsigned long long* diff, hipStream_t s);
 hipError_t launch_fill(float* p, float v, long long n, hipStream_t s);
 hipError_t launch_eval(int layout, int mode, const EvalArgs& a, hipStream_t s);

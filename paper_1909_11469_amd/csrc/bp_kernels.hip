@@ -2184,9 +2184,8 @@ __global__ void k_close_run(EvalArgs a, unsigned int* host, int words) {
         host[i] = __hip_atomic_load(&st[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void k_init_state(DevState* st, CounterLine* ctr) {
+__global__ void k_init_state(DevState* st, int nw, CounterLine* ctr) {
     unsigned int* w = (unsigned int*)st;
-    const int nw = (int)(sizeof(DevState) / sizeof(unsigned int));
     for (int i = threadIdx.x; i < nw; i += blockDim.x) w[i] = 0u;
     unsigned int* c = (unsigned int*)ctr;
     const int nc = (int)(4 * kCounterCopies * sizeof(CounterLine) / sizeof(unsigned int));
@@ -4130,8 +4129,8 @@ __global__ void k_fill_u32(unsigned int* p, unsigned int v, long long n) {
 // ---------------------------------------------------------------------------
 // Launch wrappers
 // ---------------------------------------------------------------------------
-hipError_t launch_init_state(DevState* st, CounterLine* ctr, hipStream_t s) {
-    k_init_state<<<1, 256, 0, s>>>(st, ctr);
+hipError_t launch_init_state(DevState* st, size_t bytes, CounterLine* ctr, hipStream_t s) {
+    k_init_state<<<1, 256, 0, s>>>(st, (int)(bytes / sizeof(unsigned int)), ctr);
     return hipGetLastError();
 }
 
