@@ -235,7 +235,8 @@ typedef struct bp_graph_info {
                                  first run of at least 32 iterations times 8 launches at
                                  each of 1, 2, 4 blocks per compute unit and every
                                  resident block, and keeps the fastest; results do not
-                                 depend on it); 0 until tuned */
+                                 depend on it); 0 until tuned (graphs small enough
+                                 for one block's solve are not) */
     int32_t heavy_slots;      /* layout 2: messages whose source variable has many
                                  states, neighbours or table entries, each evaluated
                                  by a wave of its own (the others share one wave per
@@ -275,8 +276,8 @@ int bp_run(bp_graph* g, int schedule, double eps, double p, uint64_t seed,
  * messages, statistics and iteration state are bitwise those of bp_run),
  * except:
  *   - the run's scratch (iteration state, per-iteration counters and the
- *     top-k tie counts: about 49 KiB plus 4 bytes per 4096 messages) is taken
- *     from a static device array of 1 MiB that each GPU holds until the
+ *     top-k tie counts: about 65 KiB plus 4 bytes per 4096 messages) is taken
+ *     from a static device array of 1056 KiB that each GPU holds until the
  *     process ends, not from the graph's memory; a graph whose scratch would
  *     not fit (more than about 1.0e9 messages) is rejected with BP_EINVAL;
  *   - no HIP events are created: stats->device_ms and the profile fields are

@@ -1634,14 +1634,11 @@ __global__ __launch_bounds__(kBlock) void k_eval_split(EvalArgs a) {
 
 // K up to 16 (shared tables; K = 2 also Ising and per-slot tables): a thread per
 // slot, every K compiled, so that the products are K * K multiply-adds that take
-// the table from scalar registers.  (One width per power of two, the states past
-// K predicated away, took 428 us for ten RnBP sweeps of a 300 x 300 grid with
-// K = 5 and 616 us for nine LBP sweeps with K = 13.)  K = 8 asks the register
-// allocator for five waves per SIMD (96 registers; 99 unconstrained): the kernel
-// waits on memory, so more resident waves pay for a spilled register or two.
+// the table from scalar registers.  (One width per power of two, the states past K
+// predicated away, took 428 us for ten RnBP sweeps of a 300 x 300 grid with
+// K = 5 and 616 us for nine LBP sweeps with K = 13.)
 template <int KP, int MODE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(KP == 8 ? 5 : 1)))
-void k_eval_generic(EvalArgs a) {
+__global__ __launch_bounds__(kBlock) void k_eval_generic(EvalArgs a) {
     extern __shared__ float smem[];
     __shared__ RedScratch red;
     __shared__ unsigned long long s_red[2];
